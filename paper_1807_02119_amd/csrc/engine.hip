@@ -291,17 +291,22 @@ __device__ __attribute__((always_inline)) void knot_setup(const DevProg& p, cons
     xm[m] = x;
   }
   __syncthreads();
-  // vertex tensors, one wavefront per tensor.  A wavefront takes its
-  // vertices 64 at a time: lane l first loads the records of vertex l of the
+  // vertex tensors, one wavefront per tensor.  Every wavefront gets an equal
+  // run of the vertices (runs of 64 left all but the first wavefront idle on
+  // knots of up to 64 vertices: a launch of 64 knots of 50-200 crossings took
+  // 257 us with them, 223 so) and takes it 64 at a time: lane l first loads the records of vertex l of the
   // block and its slot list (all lanes at once), and each vertex's values
   // are then read from its lane, so a vertex waits only for its weights
   const int lane = tid & 63, wv = tid >> 6;
   const int q = kd.q;
   const QDiv D(q);
   constexpr int kSlots = 7;  // the planner rejects vertex tensors with more slots
-  for (int v0 = wv * 64; v0 < kd.n_vtx; v0 += kBlock) {
+  constexpr int kWaves = kBlock / 64;
+  const int v_run = (kd.n_vtx + kWaves - 1) / kWaves;
+  const int v_end = min(kd.n_vtx, (wv + 1) * v_run);
+  for (int v0 = wv * v_run; v0 < v_end; v0 += 64) {
     const int mine = v0 + lane;
-    const bool have = mine < kd.n_vtx;
+    const bool have = mine < v_end;
     VtxDesc my{};
     int64_t my_off = 0;
     int32_t my_size = 0, my_lds = -1;
@@ -323,7 +328,7 @@ __device__ __attribute__((always_inline)) void knot_setup(const DevProg& p, cons
 #pragma unroll
     for (int j = 0; j < kSlots; ++j)
       wl[j] = have && j < my.n_slots ? xm[sl[j]] : Cx<double>{1.0, 0.0};
-    const int nv = min(64, kd.n_vtx - v0);
+    const int nv = min(64, v_end - v0);
     for (int u = 0; u < nv; ++u) {
       // uniform values of vertex v0 + u, read from its lane
       auto from = [u](int32_t v) { return __builtin_amdgcn_readlane(v, u); };
