@@ -226,6 +226,15 @@ struct States {
   }
 };
 
+// threadIdx.x as a value of this task: without it every expression of the
+// thread's index alone is computed before the task loop and held in registers
+// (or scratch memory) through all of it.
+__device__ inline int32_t task_tid() {
+  int32_t t = threadIdx.x;
+  asm volatile("" : "+v"(t));
+  return t;
+}
+
 // ------------------------------------------------------------------ reductions
 
 template <class T>
@@ -260,7 +269,7 @@ __device__ inline double rl_double(double x, int u) {
 template <class T>
 __device__ __attribute__((always_inline)) void knot_setup(const DevProg& p, const KnotDesc& kd, Cx<T>* arena, Cx<T>* lds,
                            const double* J, const States& st, int32_t slice) {
-  const int tid = threadIdx.x;
+  const int tid = task_tid();
   const ImgHeader& h = *p.h;
   Cx<double>* xe = p.weights + kd.w_off;
   Cx<double>* xm = xe + kd.n_edges;
@@ -714,6 +723,7 @@ __device__ __attribute__((always_inline)) void serial_steps(const DevProg& p, in
       tk = t;
     }
   };
+  const int32_t tid = task_tid();
   constexpr int32_t kDescWords = (int32_t)(sizeof(StepDesc) / 4);
   const QDiv D(q);
   // the staging area follows the tensor arena
@@ -726,7 +736,7 @@ __device__ __attribute__((always_inline)) void serial_steps(const DevProg& p, in
     {
       const int32_t* src = reinterpret_cast<const int32_t*>(p.steps + s);
       int32_t* dst = reinterpret_cast<int32_t*>(s_desc);
-      for (int32_t i = threadIdx.x; i < nd * kDescWords; i += kBlock) dst[i] = src[i];
+      for (int32_t i = tid; i < nd * kDescWords; i += kBlock) dst[i] = src[i];
     }
     __syncthreads();
     // steps of this chunk: as many as fit the table buffer (at least one)
@@ -734,20 +744,20 @@ __device__ __attribute__((always_inline)) void serial_steps(const DevProg& p, in
     for (int32_t j = 0; j < nd; ++j) {
       const int32_t e = tab_end + step_tab_entries(s_desc[j]);
       if (e > kTabBuf) break;
-      if (threadIdx.x == 0) s_tb[j] = tab_end;
+      if (tid == 0) s_tb[j] = tab_end;
       ce = j + 1;
       tab_end = e;
     }
-    if (threadIdx.x == 0) s_tb[ce] = tab_end;
+    if (tid == 0) s_tb[ce] = tab_end;
     // states of operands made before this task (already final) are fetched now
-    if (threadIdx.x < 2 * ce) {
-      const int32_t j = threadIdx.x >> 1;
-      const int32_t t = (threadIdx.x & 1) ? s_desc[j].b : s_desc[j].a;
-      if (!st.local(t)) s_ext[threadIdx.x] = p.ts[t];
+    if (tid < 2 * ce) {
+      const int32_t j = tid >> 1;
+      const int32_t t = (tid & 1) ? s_desc[j].b : s_desc[j].a;
+      if (!st.local(t)) s_ext[tid] = p.ts[t];
     }
     __syncthreads();
     // generate the gather tables: entry i belongs to step j (binary search)
-    for (int32_t i = threadIdx.x; i < tab_end; i += kBlock) {
+    for (int32_t i = tid; i < tab_end; i += kBlock) {
       int32_t lo = 0, hi = ce - 1;
       while (lo < hi) {
         const int32_t mid = (lo + hi + 1) >> 1;
@@ -791,15 +801,15 @@ __device__ __attribute__((always_inline)) void serial_steps(const DevProg& p, in
         if (je - j > 1 && (int64_t)d.nb * d.nm * d.nn * d.nk < kWaveMacs) continue;
         int64_t ec;
         T lm = serial_step<T>(d, s_tab + s_tb[u], arena, lds, st, s_ext + 2 * u,
-                              (int32_t)threadIdx.x, kBlock, stage_off, stage_elems, ec);
+                              tid, kBlock, stage_off, stage_elems, ec);
         lm = block_max<T>(lm, s_red);
-        if (threadIdx.x == 0) st.set(d.c, frexp_shift<T>(lm), ec);
+        if (tid == 0) st.set(d.c, frexp_shift<T>(lm), ec);
       }
       if (je - j > 1) {
         // the wavefront index is uniform within a wavefront: readfirstlane
         // lets the step's descriptor live in scalar registers
-        const int32_t wv = __builtin_amdgcn_readfirstlane((int32_t)(threadIdx.x >> 6));
-        const int32_t lane = threadIdx.x & 63;
+        const int32_t wv = __builtin_amdgcn_readfirstlane((int32_t)(tid >> 6));
+        const int32_t lane = tid & 63;
         int32_t r = 0;  // rank among the level's small steps
         for (int32_t u = j; u < je; ++u) {
           const StepDesc& d = s_desc[u];
@@ -852,13 +862,13 @@ __device__ inline GenIx step_ix(const DevProg& p, const StepDesc& s, int32_t q) 
 // contracted range ks of the split.  Tile tasks use none of the serial-task
 // LDS areas, so the whole dynamic LDS (tab_cap entries) holds generated offset
 // tables: contracted group first (only this task's segment of it when the
-// contracted index is split), then columns, rows, batch; the last 16 entries
+// contracted index is split), then columns, rows, batch; the last entries
 // are kept for the partial sums of a one-output tile.
 //
 // A tile of one output over a long segment (the scalar product that ends a
-// knot's contraction, split over many tasks) is summed by all four
-// wavefronts, a quarter of the segment each; wavefront 0's thread 0 adds the
-// four partial sums in wavefront order.
+// knot's contraction, split over many tasks) is summed by all wavefronts, an
+// equal part of the segment each; thread 0 adds the partial sums in wavefront
+// order.
 //
 // ph (traced launches, thread 0; else null; ph[3] holds the task's start):
 // from the start to the end of the tables and operand states, then the
@@ -867,6 +877,7 @@ template <class T>
 __device__ __attribute__((always_inline)) void tile_step(const DevProg& p, const StepDesc& s, int32_t tile_id, int32_t q,
                           Cx<T>* arena, int32_t* s_tab, int32_t tab_cap, const States& st,
                           T* s_red, int64_t* ph) {
+  const int32_t tid = task_tid();
   GenIx ix = step_ix(p, s, q);
   const int64_t outs = (int64_t)s.nb * s.nm * s.nn;
   const int32_t base = s.n_tiles / s.n_ks;
@@ -874,7 +885,8 @@ __device__ __attribute__((always_inline)) void tile_step(const DevProg& p, const
   const int32_t k0 = ks * s.kseg, k1 = min(s.nk, k0 + s.kseg);
   const int64_t o0 = (int64_t)t * s.tile;
   const int64_t o1 = o0 + s.tile < outs ? o0 + s.tile : outs;
-  constexpr int32_t kPartials = 16;  // 4 complex partial sums (64 bytes)
+  constexpr int32_t kWaves = kBlock / 64;
+  constexpr int32_t kPartials = 4 * kWaves;  // a complex partial sum (16 bytes) per wavefront
   const int32_t n_of[6] = {s.nb, s.nm, k1 - k0, s.nb, k1 - k0, s.nn};
   ix.klo = k0;
   int32_t used = 0;
@@ -882,7 +894,7 @@ __device__ __attribute__((always_inline)) void tile_step(const DevProg& p, const
     if (used + n_of[g] > tab_cap - 2 * kPartials) continue;
     const int32_t lo = g == 2 || g == 4 ? k0 : 0;
     int32_t* tb = s_tab + used;
-    for (int32_t i = threadIdx.x; i < n_of[g]; i += kBlock)
+    for (int32_t i = tid; i < n_of[g]; i += kBlock)
       tb[i] = group_off(lo + i, ix.str[g], ix.rank[g], ix.D);
     ix.tab[g] = tb;
     used += n_of[g];
@@ -901,9 +913,9 @@ __device__ __attribute__((always_inline)) void tile_step(const DevProg& p, const
   T lm = 0;
   if (o1 - o0 == 1 && k1 - k0 >= 2 * kBlock) {
     LdsCx<T>* part = (LdsCx<T>*)(s_tab + ((used + 3) & ~3));  // 16-byte aligned
-    const int32_t w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int32_t quarter = (k1 - k0 + 3) / 4;
-    const int32_t kw0 = min(k1, k0 + w * quarter), kw1 = min(k1, kw0 + quarter);
+    const int32_t w = tid >> 6, lane = tid & 63;
+    const int32_t run = (k1 - k0 + kWaves - 1) / kWaves;
+    const int32_t kw0 = min(k1, k0 + w * run), kw1 = min(k1, kw0 + run);
     const int32_t mn = s.nm * s.nn, o = (int32_t)o0;
     const int32_t b = o / mn, m = (o - b * mn) / s.nn, n = o - b * mn - m * s.nn;
     T cr, ci;
@@ -914,9 +926,9 @@ __device__ __attribute__((always_inline)) void tile_step(const DevProg& p, const
     }
     if (lane == 0) put(part, w, Cx<T>{cr, ci});
     __syncthreads();
-    if (threadIdx.x == 0) {
+    if (tid == 0) {
       T re = 0, im = 0;
-      for (int i = 0; i < 4; ++i) {
+      for (int i = 0; i < kWaves; ++i) {
         re += part[i].re;
         im += part[i].im;
       }
@@ -928,7 +940,7 @@ __device__ __attribute__((always_inline)) void tile_step(const DevProg& p, const
   } else {
     const int32_t L = lanes_per_output(o1 - o0, k1 - k0);
     lm = step_outputs<T>(pa, pb, GlbOut<T>((GlbCx<T>*)pc + o0), ix, s.nm, s.nn, k0, k1, o0, o1,
-                         scale, L, (int32_t)threadIdx.x, kBlock);
+                         scale, L, tid, kBlock);
   }
   if (ph) {
     const int64_t t = wall_clock64();
@@ -963,40 +975,255 @@ struct Mfma<float> {
   static __device__ inline int32_t row(int32_t l, int32_t r) { return 4 * (l >> 4) + r; }
 };
 
-// STEP_GEMM / STEP_GEMM64: BM x BM output blocks of C[b] (BM = 16 TM: 32
-// or 64) over contracted range ks of the split, `tile` consecutive blocks per
-// task.  Chunks of 16 contracted entries of A (BM rows) and B (BM columns)
-// are gathered into LDS (row pitch BM + 1 entries), the next chunk's operands
-// loaded into registers while the current one is multiplied.  The products
-// run on the matrix cores: the four wavefronts split the block into 2 x 2
-// quarters of WT x WT tiles of 16 x 16 (WT = TM / 2), and a complex tile
-// takes four real MFMAs per 4 contracted entries,
+// STEP_GEMM / STEP_GEMM64: output blocks of 32 x 32 or 64 x 64 entries of C[b]
+// over contracted range ks of the split, `tile` consecutive blocks per task.
+//
+// gemm_block computes BR rows and BC columns of C[b] from (m0, n0).  Chunks of
+// 16 contracted entries of A (BR rows) and B (BC columns) are gathered into
+// LDS (row pitch BR + 1 or BC + 1 entries), in two buffers in turn, the next
+// chunk's operands loaded into registers while the current one is multiplied:
+// one barrier per chunk.  The products run on the matrix cores, a complex
+// 16 x 16 tile taking four real MFMAs per 4 contracted entries,
 //   Re += Re A Re B, Re += (-Im A) Im B, Im += Re A Im B, Im += Im A Re B.
-// The contributions go to independent accumulators (with one tile per
-// wavefront the real and imaginary parts are split once more) so that
-// consecutive MFMAs do not wait on each other.  The contracted offsets come
-// from a table generated in LDS when the range fits, else they are decoded
-// from the strides.
-template <class T, int TM>
+// Regions of 64 x 32 and more: the eight wavefronts share the tiles out, 4 x 2
+// (8 x 1 for 128 x 32).  32 x 32: a wavefront has the real or the imaginary part of one of the four
+// tiles, its two products in accumulators of their own; the imaginary parts go
+// through LDS to the wavefront that holds the tile's real part, which stores
+// whole entries.  Either way consecutive MFMAs do not wait on each other.
+//
+// A gathered entry is multiplied with BC columns or BR rows, so a 128 x 128
+// region gathers half as much per product as a 64 x 64 block.  Gathers are
+// what bounds wide steps: their operands are stored in the order of the steps
+// that made them, so a wavefront's 64 entries come from up to 64 lines.
+template <class T>
+struct GemmCtx {
+  const GlbCx<T>* A;
+  const GlbCx<T>* B;
+  GlbCx<T>* C;
+  const int32_t* str;   // the step's strides (LDS): A_b A_m A_k B_b B_k B_n
+  const int32_t* ktab;  // contracted offsets of A and B in turn (LDS), or null: decode
+  int32_t rb, rm, rk, rn;
+  int32_t nm, nn, k0, kl;
+  T scale;
+  uint8_t* buf;         // LDS of the chunk buffers and row and column offsets
+  QDiv D;
+};
+
+// LDS bytes gemm_block uses.
+// Contracted entries per chunk: 8 for the largest region, whose accumulators
+// leave registers for half the operands in flight.
+template <int BR, int BC>
+constexpr int32_t gemm_chunk() {
+  return BR * BC >= 128 * 128 ? 8 : 16;
+}
+template <class T, int BR, int BC>
+constexpr int32_t gemm_lds() {
+  return 2 * gemm_chunk<BR, BC>() * (BR + 1 + BC + 1) * (int32_t)sizeof(Cx<T>) + (BR + BC) * 4;
+}
+
+template <class T, int BR, int BC>
+__device__ __attribute__((always_inline)) T gemm_block(const GemmCtx<T>& g, int32_t b, int32_t m0, int32_t n0) {
+  constexpr int32_t BK = gemm_chunk<BR, BC>(), PA = BR + 1, PB = BC + 1;
+  constexpr int32_t LR = kBlock / BK;           // rows (columns) loaded at once
+  constexpr int32_t NLA = BR / LR, NLB = BC / LR;
+  constexpr bool kParts = BR == 32;             // a wavefront has one part of one tile
+  constexpr int32_t WR = BR == 128 && BC == 32 ? 8 : 4, WC = 8 / WR;  // wavefronts by rows, columns
+  constexpr int32_t NR = kParts ? 1 : BR / (16 * WR), NC = kParts ? 1 : BC / (16 * WC);  // tiles each
+  static_assert(kBlock == 512 && BR % LR == 0 && BC % LR == 0 && BR % 32 == 0 && BC % 32 == 0 &&
+                    (kParts ? BC == 32 : BR % (16 * WR) == 0 && BC % (16 * WC) == 0),
+                "thread layout: eight wavefronts");
+  using M = Mfma<T>;
+  using V = typename M::V;
+  const int32_t tid = task_tid();
+  Cx<T>* As = reinterpret_cast<Cx<T>*>(g.buf);
+  Cx<T>* Bs = As + 2 * BK * PA;
+  int32_t* rtab = reinterpret_cast<int32_t*>(Bs + 2 * BK * PB);
+  int32_t* ctab = rtab + BR;
+  // offsets of the rows of A and the columns of B, -1 past the edge
+  const int32_t* sab = g.str;
+  const int32_t* sam = sab + g.rb;
+  const int32_t* sak = sam + g.rm;
+  const int32_t* sbb = sak + g.rk;
+  const int32_t* sbk = sbb + g.rb;
+  const int32_t* sbn = sbk + g.rk;
+  if (tid < BR) {
+    const int32_t m = m0 + tid;
+    rtab[tid] = m < g.nm ? group_off(b, sab, g.rb, g.D) + group_off(m, sam, g.rm, g.D) : -1;
+  } else if (tid < BR + BC) {
+    const int32_t n = n0 + tid - BR;
+    ctab[tid - BR] = n < g.nn ? group_off(b, sbb, g.rb, g.D) + group_off(n, sbn, g.rn, g.D) : -1;
+  }
+  __syncthreads();
+  // this thread's loads: contracted entry kk of rows / columns lr + LR i
+  const int32_t kk = tid & (BK - 1), lr = tid / BK;
+  int32_t ra[NLA], cb[NLB];
+#pragma unroll
+  for (int i = 0; i < NLA; ++i) ra[i] = rtab[lr + LR * i];
+#pragma unroll
+  for (int i = 0; i < NLB; ++i) cb[i] = ctab[lr + LR * i];
+  // this wavefront's tiles (the first at row qr, column qc), the part it has
+  // of them (kParts), and its lane
+  const int32_t lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const bool imag = kParts && wv >= 4;
+  const int32_t qr = kParts ? ((wv >> 1) & 1) * 16 : (wv / WC) * 16 * NR;
+  const int32_t qc = kParts ? (wv & 1) * 16 : (wv % WC) * 16 * NC;
+  const int32_t l16 = lane & 15, lk = lane >> 4;
+  struct Ops {
+    Cx<T> a[NLA], b[NLB];
+  };
+  auto load = [&](int32_t c0) -> Ops {
+    const int32_t k = c0 + kk;
+    Ops x;
+#pragma unroll
+    for (int i = 0; i < NLA; ++i) x.a[i] = Cx<T>{0, 0};
+#pragma unroll
+    for (int i = 0; i < NLB; ++i) x.b[i] = Cx<T>{0, 0};
+    if (k < g.kl) {
+      int32_t oa, ob;
+      if (g.ktab) {
+        oa = g.ktab[2 * k];
+        ob = g.ktab[2 * k + 1];
+      } else {
+        oa = group_off(g.k0 + k, sak, g.rk, g.D);
+        ob = group_off(g.k0 + k, sbk, g.rk, g.D);
+      }
+#pragma unroll
+      for (int i = 0; i < NLA; ++i)
+        if (ra[i] >= 0) x.a[i] = ldc(g.A + ra[i] + oa);
+#pragma unroll
+      for (int i = 0; i < NLB; ++i)
+        if (cb[i] >= 0) x.b[i] = ldc(g.B + cb[i] + ob);
+    }
+    return x;
+  };
+  // accumulators: the real and imaginary part of each tile, or the two
+  // products of one part of one tile
+  V acc0[NR][NC], acc1[NR][NC];
+#pragma unroll
+  for (int i = 0; i < NR; ++i)
+#pragma unroll
+    for (int j = 0; j < NC; ++j) {
+      acc0[i][j] = V{0, 0, 0, 0};
+      acc1[i][j] = V{0, 0, 0, 0};
+    }
+  // products of 4 contracted entries from row kr of the staged chunk
+  auto products = [&](const Cx<T>* Ac, const Cx<T>* Bc, int32_t kr) {
+    Cx<T> a[NR], bb[NC];
+#pragma unroll
+    for (int i = 0; i < NR; ++i) a[i] = Ac[(kr + lk) * PA + qr + 16 * i + l16];
+#pragma unroll
+    for (int j = 0; j < NC; ++j) bb[j] = Bc[(kr + lk) * PB + qc + 16 * j + l16];
+    if constexpr (kParts) {
+      acc0[0][0] = M::mac(a[0].re, imag ? bb[0].im : bb[0].re, acc0[0][0]);
+      acc1[0][0] = M::mac(imag ? a[0].im : -a[0].im, imag ? bb[0].re : bb[0].im, acc1[0][0]);
+    } else {
+      // the four contributions in turn over the tiles: an accumulator is
+      // used again only after every other one
+#pragma unroll
+      for (int i = 0; i < NR; ++i)
+#pragma unroll
+        for (int j = 0; j < NC; ++j) acc0[i][j] = M::mac(a[i].re, bb[j].re, acc0[i][j]);
+#pragma unroll
+      for (int i = 0; i < NR; ++i)
+#pragma unroll
+        for (int j = 0; j < NC; ++j) acc1[i][j] = M::mac(a[i].re, bb[j].im, acc1[i][j]);
+#pragma unroll
+      for (int i = 0; i < NR; ++i)
+#pragma unroll
+        for (int j = 0; j < NC; ++j) acc0[i][j] = M::mac(-a[i].im, bb[j].im, acc0[i][j]);
+#pragma unroll
+      for (int i = 0; i < NR; ++i)
+#pragma unroll
+        for (int j = 0; j < NC; ++j) acc1[i][j] = M::mac(a[i].im, bb[j].re, acc1[i][j]);
+    }
+  };
+  Ops x = load(0);
+  int32_t cur = 0;
+  for (int32_t c0 = 0; c0 < g.kl; c0 += BK) {
+    Cx<T>* Ac = As + cur * BK * PA;
+    Cx<T>* Bc = Bs + cur * BK * PB;
+#pragma unroll
+    for (int i = 0; i < NLA; ++i) Ac[kk * PA + lr + LR * i] = x.a[i];
+#pragma unroll
+    for (int i = 0; i < NLB; ++i) Bc[kk * PB + lr + LR * i] = x.b[i];
+    // a buffer is written again two chunks on, past the barrier that every
+    // wavefront reaches only once it has read it
+    __syncthreads();
+    if (c0 + BK < g.kl) x = load(c0 + BK);
+    // only the groups of 4 contracted entries this chunk holds (a short
+    // contracted index, K = 3 or 9, would otherwise multiply zero padding)
+    const int32_t kv = min(BK, g.kl - c0);
+#pragma unroll 1
+    for (int32_t j4 = 0; j4 < kv; j4 += 4) products(Ac, Bc, j4);
+    cur ^= 1;
+  }
+  __syncthreads();  // the next block's offsets and chunks overwrite this one's
+  // this wavefront's rows of C from C[b, m0 + qr, n0] (at most 32 rows: the
+  // planner keeps 64 rows of C within one output range)
+  const GlbOut<T> out(g.C + ((int64_t)b * g.nm + m0 + qr) * g.nn + n0);
+  T lm = 0;
+  if constexpr (kParts) {
+    // register r of lane l of tile t at 256 t + 64 r + l of the first buffer
+    static_assert(4 * 4 * 64 * sizeof(T) <= 2 * BK * PA * sizeof(Cx<T>), "exchange fits in As");
+    T* xch = reinterpret_cast<T*>(As) + (wv & 3) * 256;
+    if (imag) {
+#pragma unroll
+      for (int rr = 0; rr < 4; ++rr) xch[64 * rr + lane] = acc0[0][0][rr] + acc1[0][0][rr];
+    }
+    __syncthreads();
+    if (!imag) {
+      acc0[0][0] += acc1[0][0];
+#pragma unroll
+      for (int rr = 0; rr < 4; ++rr) acc1[0][0][rr] = xch[64 * rr + lane];
+    }
+    __syncthreads();
+  }
+  if (!imag) {
+#pragma unroll
+    for (int i = 0; i < NR; ++i)
+#pragma unroll
+      for (int j = 0; j < NC; ++j) {
+        const int32_t nc = qc + 16 * j + l16;
+#pragma unroll
+        for (int rr = 0; rr < 4; ++rr) {
+          const int32_t mr = 16 * i + M::row(lane, rr);
+          if (m0 + qr + mr < g.nm && n0 + nc < g.nn) {
+            const T vr = acc0[i][j][rr] * g.scale, vi = acc1[i][j][rr] * g.scale;
+            put(out, mr * g.nn + nc, Cx<T>{vr, vi});
+            lm = fmax(lm, fmax(fabs(vr), fabs(vi)));
+          }
+        }
+      }
+  }
+  return lm;
+}
+
+// One task of a STEP_GEMM (W = false) or STEP_GEMM64 step.  The blocks of a
+// batch index are counted two rows of blocks at a time, column after column, so
+// that consecutive blocks make up a larger region (four of 64 x 64: 128 x 128;
+// two: 128 x 64; four of 32 x 32: 64 x 64, or 128 x 32 in a single column; two:
+// 64 x 32), and a task of several blocks computes such regions: fewer gathers
+// per product, and one round of barriers in place of several.  A task of
+// single blocks (a step with few blocks, spread over the device) computes just
+// that block.  The contracted offsets come from a table generated in LDS when
+// the range fits, else they are decoded from the strides.
+template <class T, bool W>
 __device__ __attribute__((always_inline)) void gemm_tile(const DevProg& p, const StepDesc& s, int32_t tile_id, int32_t q,
                           Cx<T>* __restrict__ arena, uint8_t* smem, int32_t smem_bytes,
                           const States& st, T* s_red, int64_t* ph) {
-  constexpr int32_t BM = 16 * TM, BK = kGemmChunk, P = BM + 1;
-  constexpr int32_t WT = TM / 2;             // 16 x 16 tiles per wavefront side
-  constexpr int32_t NS = WT == 1 ? 2 : 1;    // accumulator chains per part
-  static_assert(BK == 16 && kBlock == 256, "thread layout: 16 x 16 threads, 16 entries per chunk");
-  using M = Mfma<T>;
-  using V = typename M::V;
-  const QDiv D(q);
+  constexpr int32_t BM = W ? 64 : 32;
+  const int32_t tid = task_tid();
   const int32_t rb = s.ranks & 255, rm = (s.ranks >> 8) & 255, rk = (s.ranks >> 16) & 255,
                 rn = (s.ranks >> 24) & 255;
-  const int32_t* sab = p.strides + s.str;
-  const int32_t* sam = sab + rb;
-  const int32_t* sak = sam + rm;
-  const int32_t* sbb = sak + rk;
-  const int32_t* sbk = sbb + rb;
-  const int32_t* sbn = sbk + rk;
-  const int32_t tid = threadIdx.x;
+  // LDS: the step's strides, the contracted offsets, then gemm_block's own
+  constexpr int32_t kStr = 128;  // the decoded groups' ranks are below 32
+  constexpr int32_t kOwn = W ? (gemm_lds<T, 128, 128>() > gemm_lds<T, 128, 64>() ? gemm_lds<T, 128, 128>() : gemm_lds<T, 128, 64>())
+                             : (gemm_lds<T, 64, 64>() > gemm_lds<T, 128, 32>() ? gemm_lds<T, 64, 64>() : gemm_lds<T, 128, 32>());
+  int32_t* str = reinterpret_cast<int32_t*>(smem + kOwn);
+  int32_t* ktab = str + kStr;
+  const int32_t kcap = (smem_bytes - kOwn - kStr * 4) / 8;
+  const int32_t n_str = 2 * rb + rm + 2 * rk + rn;
+  for (int32_t i = tid; i < n_str; i += kBlock) str[i] = p.strides[s.str + i];
   // this task: contracted range ks of the split, blocks [blk0, blk1) of the
   // nb * n_mb * n_nb blocks (s.tile blocks per task)
   const int32_t mb_nb = s.n_mb * s.n_nb;
@@ -1006,158 +1233,60 @@ __device__ __attribute__((always_inline)) void gemm_tile(const DevProg& p, const
   const int32_t ks = tile_id / base;
   const int32_t blk0 = (tile_id - ks * base) * per, blk1 = min(nblk, blk0 + per);
   const int32_t k0 = ks * s.kseg, k1 = min(s.nk, k0 + s.kseg), kl = k1 - k0;
-
-  Cx<T>* As = reinterpret_cast<Cx<T>*>(smem);
-  Cx<T>* Bs = As + BK * P;
-  int32_t* ktab = reinterpret_cast<int32_t*>(Bs + BK * P);
-  const int32_t kcap = (smem_bytes - 2 * BK * P * (int32_t)sizeof(Cx<T>)) / 8;
-  const bool use_tab = kl <= kcap;
-  if (use_tab) {
-    for (int32_t i = tid; i < kl; i += kBlock) {
-      ktab[2 * i] = group_off(k0 + i, sak, rk, D);
-      ktab[2 * i + 1] = group_off(k0 + i, sbk, rk, D);
-    }
-  }
   int64_t ec;
   const T scale = step_scale<T>(st, s.a, s.b, ec);
-  // this thread's loads: contracted entry kk of rows / columns lr + 16 i
-  const int32_t kk = tid & (BK - 1), lr = tid >> 4;
-  // this wavefront's quarter of the block and its lane
-  const int32_t lane = tid & 63, wv = tid >> 6;
-  const int32_t qr = (wv >> 1) * 16 * WT, qc = (wv & 1) * 16 * WT;
-  const int32_t l16 = lane & 15, lk = lane >> 4;
-  const GlbCx<T>* A = (const GlbCx<T>*)(arena + s.home_a);
-  const GlbCx<T>* B = (const GlbCx<T>*)(arena + s.home_b);
   const int64_t outs = (int64_t)s.nb * s.nm * s.nn;
-  GlbCx<T>* C = (GlbCx<T>*)(s.n_ks > 1 ? arena + s.partial + (int64_t)ks * outs : arena + s.home_c);
-  T lm = 0;
+  GemmCtx<T> g{(const GlbCx<T>*)(arena + s.home_a),
+               (const GlbCx<T>*)(arena + s.home_b),
+               (GlbCx<T>*)(s.n_ks > 1 ? arena + s.partial + (int64_t)ks * outs : arena + s.home_c),
+               str, kl <= kcap ? ktab : nullptr, rb, rm, rk, rn, s.nm, s.nn, k0, kl, scale, smem,
+               QDiv(q)};
   __syncthreads();
+  if (g.ktab) {
+    for (int32_t i = tid; i < kl; i += kBlock) {
+      ktab[2 * i] = group_off(k0 + i, str + rb + rm, rk, g.D);
+      ktab[2 * i + 1] = group_off(k0 + i, str + 2 * rb + rm + rk, rk, g.D);
+    }
+  }
+  T lm = 0;
   int64_t tk = 0;
   if (ph) {
     tk = wall_clock64();
     ph[0] = tk - ph[3];
   }
-
-  struct Ops {
-    Cx<T> a[TM], b[TM];
-  };
-  for (int32_t blk = blk0; blk < blk1; ++blk) {
+  const int32_t paired = (s.n_mb & ~1) * s.n_nb;  // blocks in pairs of rows of blocks
+  for (int32_t blk = blk0; blk < blk1;) {
     const int32_t b = blk / mb_nb;
     const int32_t r = blk - b * mb_nb;
-    const int32_t mblk = r / s.n_nb, nbk = r - mblk * s.n_nb;
+    int32_t mblk, nbk;
+    int32_t take = 1;
+    if (r < paired) {
+      const int32_t pr = r / (2 * s.n_nb), rest = r - pr * 2 * s.n_nb;
+      mblk = 2 * pr + (rest & 1);
+      nbk = rest >> 1;
+      if ((rest & 1) == 0) {
+        const bool four = W || s.n_nb > 1 ? nbk + 1 < s.n_nb : r + 4 <= paired;
+        if (blk + 4 <= blk1 && four) take = 4;
+        else if (blk + 2 <= blk1) take = 2;
+      }
+    } else {
+      mblk = s.n_mb - 1;
+      nbk = r - paired;
+    }
+    T m;
     const int32_t m0 = mblk * BM, n0 = nbk * BM;
-    const int32_t oab = group_off(b, sab, rb, D), obb = group_off(b, sbb, rb, D);
-    bool am[TM], bn[TM];
-    int32_t ra[TM], cb[TM];
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
-      am[i] = m0 + lr + 16 * i < s.nm;
-      bn[i] = n0 + lr + 16 * i < s.nn;
-      ra[i] = am[i] ? oab + group_off(m0 + lr + 16 * i, sam, rm, D) : 0;
-      cb[i] = bn[i] ? obb + group_off(n0 + lr + 16 * i, sbn, rn, D) : 0;
+    if constexpr (W) {
+      if (take == 4) m = gemm_block<T, 128, 128>(g, b, m0, n0);
+      else if (take == 2) m = gemm_block<T, 128, 64>(g, b, m0, n0);
+      else m = gemm_block<T, 64, 64>(g, b, m0, n0);
+    } else {
+      if (take == 4 && s.n_nb > 1) m = gemm_block<T, 64, 64>(g, b, m0, n0);
+      else if (take == 4) m = gemm_block<T, 128, 32>(g, b, m0, n0);
+      else if (take == 2) m = gemm_block<T, 64, 32>(g, b, m0, n0);
+      else m = gemm_block<T, 32, 32>(g, b, m0, n0);
     }
-    auto load = [&](int32_t c0) -> Ops {
-      const int32_t k = c0 + kk;
-      Ops x;
-#pragma unroll
-      for (int i = 0; i < TM; ++i) {
-        x.a[i] = Cx<T>{0, 0};
-        x.b[i] = Cx<T>{0, 0};
-      }
-      if (k < kl) {
-        int32_t oa, ob;
-        if (use_tab) {
-          oa = ktab[2 * k];
-          ob = ktab[2 * k + 1];
-        } else {
-          oa = group_off(k0 + k, sak, rk, D);
-          ob = group_off(k0 + k, sbk, rk, D);
-        }
-#pragma unroll
-        for (int i = 0; i < TM; ++i) {
-          if (am[i]) x.a[i] = ldc(A + ra[i] + oa);
-          if (bn[i]) x.b[i] = ldc(B + cb[i] + ob);
-        }
-      }
-      return x;
-    };
-    // accumulators: [row tile][column tile][chain], real and imaginary parts
-    V cre[WT][WT][NS], cim[WT][WT][NS];
-#pragma unroll
-    for (int i = 0; i < WT; ++i)
-#pragma unroll
-      for (int j = 0; j < WT; ++j)
-#pragma unroll
-        for (int c = 0; c < NS; ++c) {
-          cre[i][j][c] = V{0, 0, 0, 0};
-          cim[i][j][c] = V{0, 0, 0, 0};
-        }
-    Ops x = load(0);
-    for (int32_t c0 = 0; c0 < kl; c0 += BK) {
-#pragma unroll
-      for (int i = 0; i < TM; ++i) {
-        As[kk * P + lr + 16 * i] = x.a[i];
-        Bs[kk * P + lr + 16 * i] = x.b[i];
-      }
-      __syncthreads();
-      if (c0 + BK < kl) x = load(c0 + BK);
-      // only the groups of 4 contracted entries this chunk holds (a short
-      // contracted index, K = 3 or 9, would otherwise multiply zero padding)
-      const int32_t kv = min(BK, kl - c0);
-#pragma unroll
-      for (int32_t j4 = 0; j4 < kv; j4 += 4) {
-        const int32_t kr = (j4 + lk) * P;
-        Cx<T> a[WT], bb[WT];
-#pragma unroll
-        for (int i = 0; i < WT; ++i) {
-          a[i] = As[kr + qr + 16 * i + l16];
-          bb[i] = Bs[kr + qc + 16 * i + l16];
-        }
-        // the four contributions in turn over all tiles: each accumulator is
-        // used again only after every other tile's MFMA of the same kind
-        constexpr int c2 = NS - 1;
-#pragma unroll
-        for (int i = 0; i < WT; ++i)
-#pragma unroll
-          for (int j = 0; j < WT; ++j) cre[i][j][0] = M::mac(a[i].re, bb[j].re, cre[i][j][0]);
-#pragma unroll
-        for (int i = 0; i < WT; ++i)
-#pragma unroll
-          for (int j = 0; j < WT; ++j) cim[i][j][0] = M::mac(a[i].re, bb[j].im, cim[i][j][0]);
-#pragma unroll
-        for (int i = 0; i < WT; ++i)
-#pragma unroll
-          for (int j = 0; j < WT; ++j) cre[i][j][c2] = M::mac(-a[i].im, bb[j].im, cre[i][j][c2]);
-#pragma unroll
-        for (int i = 0; i < WT; ++i)
-#pragma unroll
-          for (int j = 0; j < WT; ++j) cim[i][j][c2] = M::mac(a[i].im, bb[j].re, cim[i][j][c2]);
-      }
-      __syncthreads();
-    }
-    // the block's outputs from its first entry C[b, m0, n0] (the planner
-    // keeps BM rows of C within one output range)
-    const GlbOut<T> out(C + ((int64_t)b * s.nm + m0) * s.nn + n0);
-#pragma unroll
-    for (int i = 0; i < WT; ++i)
-#pragma unroll
-      for (int j = 0; j < WT; ++j) {
-        V vre = cre[i][j][0], vim = cim[i][j][0];
-        if constexpr (NS == 2) {
-          vre += cre[i][j][1];
-          vim += cim[i][j][1];
-        }
-        const int32_t n = n0 + qc + 16 * j + l16;
-#pragma unroll
-        for (int rr = 0; rr < 4; ++rr) {
-          const int32_t mr = qr + 16 * i + M::row(lane, rr);
-          if (m0 + mr < s.nm && n < s.nn) {
-            const T vr = vre[rr] * scale, vi = vim[rr] * scale;
-            put(out, mr * s.nn + (n - n0), Cx<T>{vr, vi});
-            lm = fmax(lm, fmax(fabs(vr), fabs(vi)));
-          }
-        }
-      }
+    lm = fmax(lm, m);
+    blk += take;
   }
   if (ph) {
     const int64_t t = wall_clock64();
@@ -1654,13 +1783,13 @@ __global__ __launch_bounds__(kBlock, 2) void engine(const uint8_t* __restrict__ 
       }
       const StepDesc sd = p.steps[td.first];
       const int32_t q = p.knots[td.knot].q;
-      const int32_t dyn = kLdsArena + p.h->lds_bytes;
+      const int32_t dyn = kLdsLimit;
       if (td.kind == TASK_REDUCE)
         reduce_step<T>(p, sd, td.count, arena, st, s_red);
       else if (sd.mode == STEP_GEMM)
-        gemm_tile<T, 2>(p, sd, td.count, q, arena, kn_dyn_smem, dyn, st, s_red, ph);
+        gemm_tile<T, false>(p, sd, td.count, q, arena, kn_dyn_smem, dyn, st, s_red, ph);
       else if (sd.mode == STEP_GEMM64)
-        gemm_tile<T, 4>(p, sd, td.count, q, arena, kn_dyn_smem, dyn, st, s_red, ph);
+        gemm_tile<T, true>(p, sd, td.count, q, arena, kn_dyn_smem, dyn, st, s_red, ph);
       else
         tile_step<T>(p, sd, td.count, q, arena, s_tab, dyn / 4, st, s_red, ph);
       if (ph) ph[3] = 0;
@@ -1774,7 +1903,7 @@ int device_cus() {
 template <class T>
 kn_status launch_engine(const ImgHeader& h, uint8_t* ws, hipStream_t st, const double* J,
                         kn_scalar* z, double* grad, int32_t grid_override, TraceRec* trace) {
-  const size_t dyn = (size_t)kLdsArena + (size_t)h.lds_bytes + (size_t)stage_bytes(h.lds_bytes);
+  const size_t dyn = kLdsLimit;
   static std::once_flag once;
   static bool attr_ok = true;
   std::call_once(once, [] {

@@ -19,7 +19,11 @@
 namespace kn {
 
 constexpr int32_t kMagic = 0x4b4e4732;  // "KNG2"
-constexpr int32_t kBlock = 256;         // threads per workgroup of the engine
+// Threads per workgroup of the engine.  One workgroup runs per compute unit
+// (its LDS fills one), so this sets how many wavefronts a compute unit has to
+// hide the latency of dependent loads: 8, two per SIMD, which is what the
+// engine's registers allow.
+constexpr int32_t kBlock = 512;
 // Fixed LDS areas of a workgroup (the tensor arena follows them):
 constexpr int32_t kTabBuf = 3072;   // gather-table entries generated per chunk of serial steps
 constexpr int32_t kDescBuf = 64;    // step descriptors staged per chunk
