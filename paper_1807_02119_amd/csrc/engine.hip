@@ -1681,7 +1681,6 @@ __global__ __launch_bounds__(kBlock, 2) void engine(const uint8_t* __restrict__ 
                                                  kn_scalar* __restrict__ zout,
                                                  TraceRec* __restrict__ trace) {
   __shared__ int32_t s_task;
-  __shared__ int32_t s_enq[3];
   __shared__ T s_red[kBlock / 64];
   __shared__ int32_t s_tb[kDescBuf + 1];
   __shared__ int64_t s_ph[4];
@@ -1723,12 +1722,17 @@ __global__ __launch_bounds__(kBlock, 2) void engine(const uint8_t* __restrict__ 
         }
       }
       s_task = t;
+      // One acquire for the workgroup, whose wavefronts share their L1; the
+      // barrier orders the others' loads after it.  These cache operations are
+      // served one after another per XCD, 50 ns each: with one per wavefront
+      // (and one to release) a task spent up to 28 us on them when all
+      // compute units were busy, 3 us so.
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     }
     __syncthreads();
     const int32_t ti = s_task;
     __syncthreads();
     if (ti < 0) break;
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     const int64_t t_start = (trace && tid == 0) ? wall_clock64() : 0;
     const TaskDesc td = p.tasks[ti];
     // a sliced unit that starts its next slice after this task (its final task)
@@ -1794,39 +1798,47 @@ __global__ __launch_bounds__(kBlock, 2) void engine(const uint8_t* __restrict__ 
         tile_step<T>(p, sd, td.count, q, arena, s_tab, dyn / 4, st, s_red, ph);
       if (ph) ph[3] = 0;
     }
-    // ---- publish; the last task of a group releases the knot's next group
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    // ---- publish; the last task of a group releases the knot's next group.
+    // Every wavefront waits for its own stores to complete: the barrier does
+    // not wait for them, and the release below, by one wavefront for all,
+    // only waits for that wavefront's.
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    if (tid == 0) {
-      s_enq[0] = 0;
-      const int32_t next = p.groups[td.group].next;
-      if (next_slice >= 0) {
-        // the unit's first group again, for its next slice
-        const GroupDesc g = p.groups[p.knots[td.knot].group_off];
-        s_enq[0] = g.n_tasks;
-        s_enq[1] = g.first_task;
-        s_enq[2] = atomicAdd(&p.ctrl[CTRL_TAIL], g.n_tasks);
-      } else if (next >= 0 && __hip_atomic_fetch_add(&p.pending[next], -1, __ATOMIC_ACQ_REL,
-                                                     __HIP_MEMORY_SCOPE_AGENT) == 1) {
-        const GroupDesc g = p.groups[next];
-        s_enq[0] = g.n_tasks;
-        s_enq[1] = g.first_task;
-        s_enq[2] = atomicAdd(&p.ctrl[CTRL_TAIL], g.n_tasks);
+    if (tid < 64) {
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      int32_t n_enq = 0, first = 0, base = 0;
+      if (tid == 0) {
+        // the group to start: the unit's first again, for its next slice, or
+        // the next one where this was the last task of its predecessor
+        int32_t start = -1;
+        const int32_t next = p.groups[td.group].next;
+        if (next_slice >= 0) start = p.knots[td.knot].group_off;
+        else if (next >= 0 && __hip_atomic_fetch_add(&p.pending[next], -1, __ATOMIC_RELAXED,
+                                                     __HIP_MEMORY_SCOPE_AGENT) == 1)
+          start = next;
+        if (start >= 0) {
+          const GroupDesc g = p.groups[start];
+          n_enq = g.n_tasks;
+          first = g.first_task;
+          base = atomicAdd(&p.ctrl[CTRL_TAIL], n_enq);
+        }
+        if (trace) {
+          TraceRec r{t_claim, t_start, wall_clock64(), ti, (int32_t)blockIdx.x, {0, 0, 0, 0}};
+          for (int i = 0; i < 4; ++i) r.ph[i] = s_ph[i];
+          trace[ti] = r;
+        }
       }
-      if (trace) {
-        TraceRec r{t_claim, t_start, wall_clock64(), ti, (int32_t)blockIdx.x, {0, 0, 0, 0}};
-        for (int i = 0; i < 4; ++i) r.ph[i] = s_ph[i];
-        trace[ti] = r;
+      n_enq = __builtin_amdgcn_readfirstlane(n_enq);
+      if (n_enq) {
+        first = __builtin_amdgcn_readfirstlane(first);
+        base = __builtin_amdgcn_readfirstlane(base);
+        // the other tasks of the finished group, through its counter
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "agent");
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        for (int32_t i = tid; i < n_enq; i += 64)
+          __hip_atomic_store(&p.queue[base + i], first + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
-    }
-    __syncthreads();
-    const int32_t n_enq = s_enq[0];
-    if (n_enq) {
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-      const int32_t first = s_enq[1], base = s_enq[2];
-      for (int32_t i = tid; i < n_enq; i += kBlock)
-        __hip_atomic_store(&p.queue[base + i], first + i, __ATOMIC_RELEASE,
-                           __HIP_MEMORY_SCOPE_AGENT);
     }
   }
 }
