@@ -21,7 +21,8 @@ namespace kn {
 // Every index QDiv::div accepts: 0 <= x <= kDecodeMax (all non-negative int32).
 constexpr int64_t kDecodeMax = 2147483647;
 
-// Exact floor(x / q) for 2 <= q <= 8 and 0 <= x < 2^31.
+// Exact floor(x / q) for q >= 2 and 0 <= x < 2^31 (q = 2..8 for spins, and
+// powers of them).
 //
 // With l = ceil(log2 q) and m = floor(2^(31+l) / q) + 1 (m < 2^32), write
 // m q = 2^(31+l) + d with 1 <= d <= q <= 2^l.  Then
@@ -40,6 +41,7 @@ struct QDiv {
     m = (uint32_t)(((uint64_t)1 << (31 + l)) / (uint64_t)q_ + 1);
     sh = l - 1;
   }
+  KN_HD QDiv(int32_t q_, uint32_t m_, int32_t sh_) : m(m_), sh(sh_), q(q_) {}
   KN_HD inline int32_t div(int32_t x) const {
     const uint32_t hi = (uint32_t)(((uint64_t)(uint32_t)x * (uint64_t)m) >> 32);
     return (int32_t)(hi >> sh);

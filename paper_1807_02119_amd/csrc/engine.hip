@@ -18,9 +18,10 @@
 //           with T = 1 + (x - 1) delta (Eqs. 3, 5); a vertex spin private to
 //           its tensor is summed here.
 //   step    C[b,m,n] = sum_k A[b,m,k] B[b,k,n] (one pairwise contraction of
-//           Eq. 6).  Operands are gathered through per-step offset tables
-//           (staged in LDS), so the permutation that brings A and B into GEMM
-//           order is fused into the loads and never materialised.  Tensors
+//           Eq. 6).  Operands are gathered from where their strides put
+//           them (decoded from digit strides, or from offset tables in LDS),
+//           so the permutation that brings A and B into GEMM order is fused
+//           into the loads and never materialised.  Tensors
 //           that live inside one serial task are kept in that workgroup's LDS.
 //           Each tensor is a raw mantissa array R with an int64 exponent e
 //           (true = R 2^e) and a shift s = frexp exponent of max(|Re|,|Im|)
@@ -198,6 +199,17 @@ __device__ inline void put(LdsCx<T>* p, int32_t i, Cx<T> v) {
   p[i].im = v.im;
 }
 
+// One entry written through the L2 by a lane on its own (where the lanes of a
+// wavefront write to different tensors, which no one buffer resource covers).
+__device__ inline void put_through(Cx<double>* p, Cx<double> v) {
+  __hip_atomic_store(&p->re, v.re, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  __hip_atomic_store(&p->im, v.im, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+__device__ inline void put_through(Cx<float>* p, Cx<float> v) {
+  __hip_atomic_store(reinterpret_cast<uint64_t*>(p), __builtin_bit_cast(uint64_t, v), __ATOMIC_RELAXED,
+                     __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Tensor states: those produced by the running serial task are cached in LDS,
 // the rest live in global memory.
 struct States {
@@ -214,6 +226,14 @@ struct States {
       shift = g[t].shift;
       e = g[t].exp2;
     }
+  }
+  // A state beyond what LDS holds that the running serial task may have
+  // updated by atomics at the L2.  (Every lane of such a load is a request of
+  // its own: tile tasks, which read their operands' states in all threads,
+  // spent 10 us more each with it.)
+  __device__ inline void get_late(int32_t t, int32_t& shift, int64_t& e) const {
+    shift = __hip_atomic_load(&g[t].shift, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    e = __hip_atomic_load(&g[t].exp2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   __device__ inline void set(int32_t t, int32_t shift, int64_t e) const {
     if (local(t)) {
@@ -244,6 +264,46 @@ __device__ inline T wave_max(T v) {
   return v;
 }
 
+// Maximum of an integer over the wavefront, in lane 63 (row shifts, then row
+// broadcasts; a lane without a source keeps its own value).
+__device__ inline int32_t wave_max_last(int32_t v) {
+#define KN_DPP_MAX(ctrl, rows) \
+  v = max(v, __builtin_amdgcn_update_dpp(v, v, ctrl, rows, 0xf, false))
+  KN_DPP_MAX(0x111, 0xf);  // row_shr:1
+  KN_DPP_MAX(0x112, 0xf);  // row_shr:2
+  KN_DPP_MAX(0x114, 0xf);  // row_shr:4
+  KN_DPP_MAX(0x118, 0xf);  // row_shr:8
+  KN_DPP_MAX(0x142, 0xa);  // row_bcast:15 into rows 1 and 3
+  KN_DPP_MAX(0x143, 0xc);  // row_bcast:31 into rows 2 and 3
+#undef KN_DPP_MAX
+  return v;
+}
+
+// Inclusive sum over the lanes up to this one.
+__device__ inline int32_t wave_scan(int32_t v) {
+#define KN_DPP_ADD(ctrl, rows) v += __builtin_amdgcn_update_dpp(0, v, ctrl, rows, 0xf, false)
+  KN_DPP_ADD(0x111, 0xf);
+  KN_DPP_ADD(0x112, 0xf);
+  KN_DPP_ADD(0x114, 0xf);
+  KN_DPP_ADD(0x118, 0xf);
+  KN_DPP_ADD(0x142, 0xa);
+  KN_DPP_ADD(0x143, 0xc);
+#undef KN_DPP_ADD
+  return v;
+}
+
+// The lane in [lo, hi) whose run of items holds item x, from the inclusive
+// sums `end` of the lanes' runs (bisection: the lanes of [lo, hi) that end at
+// or before x).
+__device__ inline int32_t lane_of(int32_t end, int32_t x, int32_t lo, int32_t hi) {
+  int32_t j = lo;
+  for (int32_t h = 1 << (31 - __clz(hi - lo)); h >= 1; h >>= 1) {
+    const int32_t e = __shfl(end, min(j + h, hi) - 1, 64);  // (every lane takes part)
+    if (j + h <= hi && e <= x) j += h;
+  }
+  return j;
+}
+
 template <class T>
 __device__ inline T block_max(T v, T* red) {
   v = wave_max(v);
@@ -258,6 +318,24 @@ __device__ inline T block_max(T v, T* red) {
 
 // ------------------------------------------------------------------ setup
 
+// Lane u's value of an integer held per lane (uniform result).
+__device__ inline int32_t rl(int32_t v, int32_t lane) { return __builtin_amdgcn_readlane(v, lane); }
+
+// Indices below 2^15 are divided by q in 24-bit arithmetic (full rate; a
+// 32-bit multiply takes four times as long): with m = ceil(2^18 / q) the
+// product x m is below 2^32, and m q exceeds 2^18 by less than q <= 8, so
+// x m / 2^18 exceeds x / q by less than 1 / q.
+constexpr int32_t kSmallIndex = 1 << 15;
+__device__ inline uint32_t small_magic(int32_t q) { return ((1u << 18) + (uint32_t)q - 1) / (uint32_t)q; }
+
+// QDiv(q) without a 64-bit integer division: 2^(31 + l) / q is below 2^32 and,
+// where it is no integer, at least 1 / q away from one, far more than the
+// rounding of the quotient in double precision for q < 2^20.
+__device__ inline QDiv qdiv_of(int32_t q) {
+  const int32_t l = 32 - __clz(q - 1);
+  return QDiv(q, (uint32_t)(__builtin_ldexp(1.0, 31 + l) / (double)q) + 1u, l - 1);
+}
+
 // Lane u's value of a double held per lane (uniform result).
 __device__ inline double rl_double(double x, int u) {
   const uint64_t b = __builtin_bit_cast(uint64_t, x);
@@ -268,7 +346,7 @@ __device__ inline double rl_double(double x, int u) {
 
 template <class T>
 __device__ __attribute__((always_inline)) void knot_setup(const DevProg& p, const KnotDesc& kd, Cx<T>* arena, Cx<T>* lds,
-                           const double* J, const States& st, int32_t slice) {
+                           LdsCx<double>* s_w, int32_t w_cap, const double* J, const States& st, int32_t slice) {
   const int tid = task_tid();
   const ImgHeader& h = *p.h;
   Cx<double>* xe = p.weights + kd.w_off;
@@ -300,104 +378,90 @@ __device__ __attribute__((always_inline)) void knot_setup(const DevProg& p, cons
     xm[m] = x;
   }
   __syncthreads();
-  // vertex tensors, one wavefront per tensor.  Every wavefront gets an equal
-  // run of the vertices (runs of 64 left all but the first wavefront idle on
-  // knots of up to 64 vertices: a launch of 64 knots of 50-200 crossings took
-  // 257 us with them, 223 so) and takes it 64 at a time: lane l first loads the records of vertex l of the
-  // block and its slot list (all lanes at once), and each vertex's values
-  // are then read from its lane, so a vertex waits only for its weights
-  const int lane = tid & 63, wv = tid >> 6;
+  // the weights of the vertices' slots (each merged edge is absorbed once), in
+  // slot order, to LDS: the loop over a vertex's entries then reads no global
+  // memory (a load there would also wait for the entries stored before it)
+  const VtxDesc* vtx = p.vtx + kd.vtx_off;
+  const int32_t slot0 = kd.n_vtx ? vtx[0].slot_off : 0;
+  const int32_t n_slot = kd.n_vtx ? vtx[kd.n_vtx - 1].slot_off + vtx[kd.n_vtx - 1].n_slots - slot0 : 0;
+  for (int32_t i = tid; i < min(n_slot, w_cap); i += kBlock) {
+    const Cx<double> x = xm[p.vslot[slot0 + i]];
+    s_w[i].re = x.re;
+    s_w[i].im = x.im;
+  }
+  __syncthreads();
+  // vertex tensors, 64 vertices at a time: lane l of every wavefront loads the
+  // records of vertex l of the block, and the block's entries, vertex after
+  // vertex, are shared out to the wavefronts 64 at a time, each lane with the
+  // vertex of its entry (a vertex has 9 to 81 entries mostly: one vertex at a
+  // time left most lanes idle, and its 300 or so instructions were what setup
+  // took).
+  const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int q = kd.q;
-  const QDiv D(q);
-  constexpr int kSlots = 7;  // the planner rejects vertex tensors with more slots
-  constexpr int kWaves = kBlock / 64;
-  const int v_run = (kd.n_vtx + kWaves - 1) / kWaves;
-  const int v_end = min(kd.n_vtx, (wv + 1) * v_run);
-  for (int v0 = wv * v_run; v0 < v_end; v0 += 64) {
-    const int mine = v0 + lane;
-    const bool have = mine < v_end;
-    VtxDesc my{};
-    int64_t my_off = 0;
-    int32_t my_size = 0, my_lds = -1;
-    if (have) {
-      my = p.vtx[kd.vtx_off + mine];
-      const TensorDesc t = p.tens[my.tensor];
-      my_off = t.off;
-      my_size = t.size;
-      my_lds = t.lds_off;
-    }
-    // the slot lists of the block, one merged-edge id per slot, and the
-    // weights x_m of those slots: loaded once per block, so that the entry
-    // loop of a vertex reads no global memory (a load there would also wait
-    // for the entries stored before it)
-    int32_t sl[kSlots];
-#pragma unroll
-    for (int j = 0; j < kSlots; ++j) sl[j] = have && j < my.n_slots ? p.vslot[my.slot_off + j] : 0;
-    Cx<double> wl[kSlots];
-#pragma unroll
-    for (int j = 0; j < kSlots; ++j)
-      wl[j] = have && j < my.n_slots ? xm[sl[j]] : Cx<double>{1.0, 0.0};
-    const int nv = min(64, v_end - v0);
-    for (int u = 0; u < nv; ++u) {
-      // uniform values of vertex v0 + u, read from its lane
-      auto from = [u](int32_t v) { return __builtin_amdgcn_readlane(v, u); };
-      const int32_t tensor = from(my.tensor);
-      const int32_t n_slots = from(my.n_slots);
-      const int32_t keep = from(my.keep_center);
-      const int32_t pin_off = from(my.pin_off);
-      const int32_t n_pins = from(my.n_pins);
-      const int32_t size = from(my_size);
-      const int32_t lds_off = from(my_lds);
-      const int64_t off = (int64_t)(((uint64_t)(uint32_t)from((int32_t)(my_off >> 32)) << 32) |
-                                    (uint32_t)from((int32_t)my_off));
-      Cx<double> w[kSlots];
-#pragma unroll
-      for (int j = 0; j < kSlots; ++j) w[j] = {rl_double(wl[j].re, u), rl_double(wl[j].im, u)};
-      const bool in_lds = lds_off >= 0;
-      Cx<T>* out = in_lds ? lds + lds_off : arena + off;
-      const GlbOut<T> gout((GlbCx<T>*)(in_lds ? arena : out));
-      for (int i = lane; i < size; i += 64) {
-        // digits of i: last neighbour slot fastest (exact division by q
-        // through a multiply-high, once per entry); a kept centre is the
-        // leading index (what is left of i after the slot digits), a private
-        // centre is summed over.  A reverse-pass seed (keep_center < 0, no
-        // slots, one entry) takes the kept branch with an empty product: the
-        // scalar 1.
-        int dig[kSlots];
-        int rem = i;
-#pragma unroll
-        for (int j = kSlots - 1; j >= 0; --j) {
-          dig[j] = -1;
-          if (j < n_slots) {
-            const int32_t qt = D.div(rem);
-            dig[j] = rem - qt * q;
-            rem = qt;
-          }
-        }
-        const int a_lo = keep ? rem : 0;
-        const int a_hi = keep ? a_lo + 1 : q;
-        Cx<double> acc{0.0, 0.0};
-        for (int a = a_lo; a < a_hi; ++a) {
-          Cx<double> prod{1.0, 0.0};
-#pragma unroll
-          for (int j = kSlots - 1; j >= 0; --j)
-            if (dig[j] == a) prod = cmul(prod, w[j]);
-          // slices: an edge to a fixed spin contributes x_m where this spin
-          // takes the fixed value (digit j of the slice number, base q)
-          for (int j = 0; j < n_pins; ++j) {
-            const int32_t* pn = p.pins + 2 * (pin_off + j);
-            int sv = slice;
-            for (int r = 0; r < pn[1]; ++r) sv /= q;
-            if (sv % q == a) prod = cmul(prod, xm[pn[0]]);
-          }
-          acc.re += prod.re;
-          acc.im += prod.im;
-        }
-        if (in_lds) out[i] = Cx<T>{(T)acc.re, (T)acc.im};
-        else put(gout, i, Cx<T>{(T)acc.re, (T)acc.im});
-      }
+  const uint32_t m18 = small_magic(q);
+  VtxDesc next{};
+  if (lane < kd.n_vtx) next = vtx[lane];
+  for (int v0 = 0; v0 < kd.n_vtx; v0 += 64) {
+    const VtxDesc my = next;
+    TensorDesc td{};
+    if (v0 + lane < kd.n_vtx) {
+      td = p.tens[my.tensor];
       // entries are products of <= 8 weights: no scaling needed
-      if (lane == 0) st.set(tensor, 0, 0);
+      if (wv == 0) st.set(my.tensor, 0, 0);
+    }
+    next = VtxDesc{};
+    if (v0 + 64 + lane < kd.n_vtx) next = vtx[v0 + 64 + lane];
+    const int32_t e_end = wave_scan(td.size);
+    const int32_t total = rl(e_end, 63);
+    for (int32_t x0 = 64 * wv; x0 < total; x0 += kBlock) {
+      const int32_t x = min(x0 + lane, total - 1);
+      const int u = lane_of(e_end, x, 0, 64);
+      const int32_t n_slots = __shfl(my.n_slots, u, 64), keep = __shfl(my.keep_center, u, 64);
+      const int32_t slot = __shfl(my.slot_off, u, 64) - slot0;
+      const int32_t i = x - (__shfl(e_end, u, 64) - __shfl(td.size, u, 64));
+      // digits of entry i, 3 bits each: last neighbour slot fastest (first
+      // here); a kept centre is the leading index (what is left after the
+      // slot digits), a private centre is summed over.  A reverse-pass seed
+      // (keep_center < 0, no slots, one entry) takes the kept branch with an
+      // empty product: the scalar 1.
+      uint32_t dig = 0, rem = (uint32_t)i;
+      for (int j = 0; j < n_slots; ++j) {
+        const uint32_t up = rem < (uint32_t)kSmallIndex ? __umul24(rem, m18) >> 18 : rem / (uint32_t)q;
+        dig |= (rem - up * (uint32_t)q) << (3 * j);
+        rem = up;
+      }
+      const int a_lo = keep ? (int)rem : 0;
+      const int a_hi = keep ? a_lo + 1 : q;
+      const int32_t pin_off = __shfl(my.pin_off, u, 64), n_pins = __shfl(my.n_pins, u, 64);
+      Cx<double> acc{0.0, 0.0};
+      for (int a = a_lo; a < a_hi; ++a) {
+        Cx<double> prod{1.0, 0.0};
+        for (int j = 0; j < n_slots; ++j) {
+          const int32_t sl = slot + n_slots - 1 - j;
+          if ((int)((dig >> (3 * j)) & 7) != a) continue;
+          Cx<double> w;
+          if (sl < w_cap) w = Cx<double>{s_w[sl].re, s_w[sl].im};
+          else w = xm[p.vslot[slot0 + sl]];
+          prod = cmul(prod, w);
+        }
+        // slices: an edge to a fixed spin contributes x_m where this spin
+        // takes the fixed value (digit j of the slice number, base q)
+        for (int j = 0; j < n_pins; ++j) {
+          const int32_t* pn = p.pins + 2 * (pin_off + j);
+          int sv = slice;
+          for (int r = 0; r < pn[1]; ++r) sv /= q;
+          if (sv % q == a) prod = cmul(prod, xm[pn[0]]);
+        }
+        acc.re += prod.re;
+        acc.im += prod.im;
+      }
+      const int32_t lds_off = __shfl(td.lds_off, u, 64);
+      const int32_t off_lo = __shfl((int32_t)td.off, u, 64), off_hi = __shfl((int32_t)(td.off >> 32), u, 64);
+      if (x0 + lane < total) {
+        const Cx<T> v{(T)acc.re, (T)acc.im};
+        if (lds_off >= 0) put((LdsCx<T>*)(lds + lds_off), i, v);
+        else put_through(arena + (int64_t)(((uint64_t)(uint32_t)off_hi << 32) | (uint32_t)off_lo) + i, v);
+      }
     }
   }
 }
@@ -410,209 +474,6 @@ __device__ inline int32_t lanes_per_output(int64_t outs, int32_t nk, int32_t nth
   int32_t L = 1;
   while (L < 64 && 2 * L <= nk && outs * L < nthr) L *= 2;
   return L;
-}
-
-// Operand offsets from generated tables (serial steps: tables in LDS).
-struct TabIx {
-  const int32_t *ab, *am, *ak, *bb, *bk, *bn;
-  __device__ inline int32_t a_row(int32_t b, int32_t m) const { return ab[b] + am[m]; }
-  __device__ inline int32_t b_col(int32_t b, int32_t n) const { return bb[b] + bn[n]; }
-  __device__ inline int32_t a_k(int32_t k) const { return ak[k]; }
-  __device__ inline int32_t b_k(int32_t k) const { return bk[k]; }
-};
-
-// Operand offsets for tiles: each spin group's offsets come from a table
-// generated in LDS when it fitted, else they are decoded from the strides.
-struct GenIx {
-  const int32_t *tab[6];  // A_b A_m A_k B_b B_k B_n (nullptr: decode)
-  const int32_t *str[6];
-  int32_t rank[6];
-  int32_t klo;            // first contracted index the A_k and B_k tables hold
-  QDiv D;
-  __device__ inline int32_t off(int g, int32_t i) const {
-    return tab[g] ? tab[g][i] : group_off(i, str[g], rank[g], D);
-  }
-  __device__ inline int32_t off_k(int g, int32_t k) const {
-    return tab[g] ? tab[g][k - klo] : group_off(k, str[g], rank[g], D);
-  }
-  __device__ inline int32_t a_row(int32_t b, int32_t m) const { return off(0, b) + off(1, m); }
-  __device__ inline int32_t b_col(int32_t b, int32_t n) const { return off(3, b) + off(5, n); }
-  __device__ inline int32_t a_k(int32_t k) const { return off_k(2, k); }
-  __device__ inline int32_t b_k(int32_t k) const { return off_k(4, k); }
-};
-
-// This lane's part of sum_k A[row, k] B[k, col] over k = k_first, k_first + L,
-// ... < nk: four entries per round, the loads of a round issued before its
-// products (entries past nk read as zero) so that a short contracted range
-// does not serialise on memory latency.
-template <class T, class Ix, class PA, class PB>
-__device__ inline void lane_dot(PA ra, PB rb, const Ix& ix, int32_t k, int32_t nk, int32_t L,
-                                T& cr, T& ci) {
-  T cr0 = 0, ci0 = 0, cr1 = 0, ci1 = 0;
-  const Cx<T> zero{0, 0};
-  for (; k < nk; k += 4 * L) {
-    const bool v1 = k + L < nk, v2 = k + 2 * L < nk, v3 = k + 3 * L < nk;
-    const Cx<T> x0 = ldc(ra + ix.a_k(k));
-    const Cx<T> y0 = ldc(rb + ix.b_k(k));
-    Cx<T> x1 = zero, y1 = zero, x2 = zero, y2 = zero, x3 = zero, y3 = zero;
-    if (v1) {
-      x1 = ldc(ra + ix.a_k(k + L));
-      y1 = ldc(rb + ix.b_k(k + L));
-    }
-    if (v2) {
-      x2 = ldc(ra + ix.a_k(k + 2 * L));
-      y2 = ldc(rb + ix.b_k(k + 2 * L));
-    }
-    if (v3) {
-      x3 = ldc(ra + ix.a_k(k + 3 * L));
-      y3 = ldc(rb + ix.b_k(k + 3 * L));
-    }
-    cr0 = fma(x0.re, y0.re, cr0); cr0 = fma(-x0.im, y0.im, cr0);
-    ci0 = fma(x0.re, y0.im, ci0); ci0 = fma(x0.im, y0.re, ci0);
-    cr1 = fma(x1.re, y1.re, cr1); cr1 = fma(-x1.im, y1.im, cr1);
-    ci1 = fma(x1.re, y1.im, ci1); ci1 = fma(x1.im, y1.re, ci1);
-    cr0 = fma(x2.re, y2.re, cr0); cr0 = fma(-x2.im, y2.im, cr0);
-    ci0 = fma(x2.re, y2.im, ci0); ci0 = fma(x2.im, y2.re, ci0);
-    cr1 = fma(x3.re, y3.re, cr1); cr1 = fma(-x3.im, y3.im, cr1);
-    ci1 = fma(x3.re, y3.im, ci1); ci1 = fma(x3.im, y3.re, ci1);
-  }
-  cr = cr0 + cr1;
-  ci = ci0 + ci1;
-}
-
-// lane_dot for two outputs at once (rows ra, ra2 and columns rb, rb2): a
-// round issues the 16 loads of four contracted entries of both before any
-// product, so a thread has twice the loads in flight of two lane_dot calls.
-// Each output is summed in the same order as by lane_dot.
-template <class T, class Ix, class PA, class PB>
-__device__ inline void lane_dot2(PA ra, PB rb, PA ra2, PB rb2, const Ix& ix, int32_t k,
-                                 int32_t nk, int32_t L, T& cr, T& ci, T& cr2, T& ci2) {
-  T p0 = 0, q0 = 0, p1 = 0, q1 = 0, u0 = 0, w0 = 0, u1 = 0, w1 = 0;
-  const Cx<T> zero{0, 0};
-  for (; k < nk; k += 4 * L) {
-    int32_t oa[4], ob[4];
-    bool v[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      v[j] = j == 0 || k + j * L < nk;
-      oa[j] = v[j] ? ix.a_k(k + j * L) : 0;
-      ob[j] = v[j] ? ix.b_k(k + j * L) : 0;
-    }
-    Cx<T> x[4], y[4], x2[4], y2[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      x[j] = zero; y[j] = zero; x2[j] = zero; y2[j] = zero;
-      if (v[j]) {
-        x[j] = ldc(ra + oa[j]);
-        y[j] = ldc(rb + ob[j]);
-        x2[j] = ldc(ra2 + oa[j]);
-        y2[j] = ldc(rb2 + ob[j]);
-      }
-    }
-#pragma unroll
-    for (int j = 0; j < 4; j += 2) {
-      p0 = fma(x[j].re, y[j].re, p0); p0 = fma(-x[j].im, y[j].im, p0);
-      q0 = fma(x[j].re, y[j].im, q0); q0 = fma(x[j].im, y[j].re, q0);
-      p1 = fma(x[j + 1].re, y[j + 1].re, p1); p1 = fma(-x[j + 1].im, y[j + 1].im, p1);
-      q1 = fma(x[j + 1].re, y[j + 1].im, q1); q1 = fma(x[j + 1].im, y[j + 1].re, q1);
-      u0 = fma(x2[j].re, y2[j].re, u0); u0 = fma(-x2[j].im, y2[j].im, u0);
-      w0 = fma(x2[j].re, y2[j].im, w0); w0 = fma(x2[j].im, y2[j].re, w0);
-      u1 = fma(x2[j + 1].re, y2[j + 1].re, u1); u1 = fma(-x2[j + 1].im, y2[j + 1].im, u1);
-      w1 = fma(x2[j + 1].re, y2[j + 1].im, w1); w1 = fma(x2[j + 1].im, y2[j + 1].re, w1);
-    }
-  }
-  cr = p0 + p1;
-  ci = q0 + q1;
-  cr2 = u0 + u1;
-  ci2 = w0 + w1;
-}
-
-// Outputs [o_begin, o_end) of C = A . B, each summed over k in [k0, nk) by L
-// lanes of one wavefront; threads tid = 0..nthr-1 (a whole workgroup or one
-// wavefront) share the outputs.  pc addresses the range itself: output o is
-// entry o - o_begin of pc.  A thread computes two outputs together (their
-// loads interleaved) before it stores either, so its stores overlap the next
-// pair's loads.  Returns this thread's max |.|.
-template <class T, class Ix, class PA, class PB, class PC>
-__device__ __attribute__((always_inline)) T step_outputs(PA pa, PB pb, PC pc, const Ix& ix, int32_t nm, int32_t nn, int32_t k0,
-                          int32_t nk, int64_t o_begin, int64_t o_end, T scale, int32_t L,
-                          int32_t tid, int32_t nthr) {
-  const int32_t mn = nm * nn;
-  const int32_t ob = (int32_t)o_begin;
-  const int32_t lsub = tid & (L - 1);
-  const int32_t slot = tid / L;
-  const int32_t nslot = nthr / L;
-  T lmax = 0;
-  for (int64_t o = o_begin + slot; o < o_end; o += 2 * nslot) {
-    const int32_t oi = (int32_t)o;
-    const int32_t oi2 = oi + nslot;
-    const bool two = oi2 < o_end;  // the same for the L lanes of an output
-    T cr, ci, cr2 = 0, ci2 = 0;
-    const int32_t b = oi / mn;
-    const int32_t r = oi - b * mn;
-    const int32_t m = r / nn;
-    const int32_t n = r - m * nn;
-    if (two) {
-      const int32_t b2 = oi2 / mn;
-      const int32_t r2 = oi2 - b2 * mn;
-      const int32_t m2 = r2 / nn;
-      const int32_t n2 = r2 - m2 * nn;
-      lane_dot2<T>(pa + ix.a_row(b, m), pb + ix.b_col(b, n), pa + ix.a_row(b2, m2),
-                   pb + ix.b_col(b2, n2), ix, k0 + lsub, nk, L, cr, ci, cr2, ci2);
-    } else {
-      lane_dot<T>(pa + ix.a_row(b, m), pb + ix.b_col(b, n), ix, k0 + lsub, nk, L, cr, ci);
-    }
-    for (int32_t off = L >> 1; off >= 1; off >>= 1) {
-      cr += __shfl_xor(cr, off, 64);
-      ci += __shfl_xor(ci, off, 64);
-      cr2 += __shfl_xor(cr2, off, 64);
-      ci2 += __shfl_xor(ci2, off, 64);
-    }
-    if (lsub == 0) {
-      cr *= scale;
-      ci *= scale;
-      put(pc, oi - ob, Cx<T>{cr, ci});
-      lmax = fmax(lmax, fmax(fabs(cr), fabs(ci)));
-      if (two) {
-        cr2 *= scale;
-        ci2 *= scale;
-        put(pc, oi2 - ob, Cx<T>{cr2, ci2});
-        lmax = fmax(lmax, fmax(fabs(cr2), fabs(ci2)));
-      }
-    }
-  }
-  return lmax;
-}
-
-// step_outputs with each operand's home (>= 0 global arena offset, < 0 LDS
-// arena offset -1 - home) resolved to a pointer of its address space.
-template <class T, class Ix>
-__device__ __attribute__((always_inline)) T step_outputs_homes(int32_t ha, int32_t hb, int32_t hc, Cx<T>* arena, Cx<T>* lds,
-                                const Ix& ix, int32_t nm, int32_t nn, int32_t k0, int32_t nk,
-                                int64_t o_begin, int64_t o_end, T scale, int32_t L, int32_t tid,
-                                int32_t nthr) {
-  auto gl = [&](int32_t h) { return (GlbCx<T>*)(arena + h); };
-  auto ld = [&](int32_t h) { return (LdsCx<T>*)(lds + (-1 - h)); };
-  // the output range [o_begin, o_end) of C
-  auto glo = [&](int32_t h) { return GlbOut<T>((GlbCx<T>*)(arena + h) + o_begin); };
-  auto ldo = [&](int32_t h) { return (LdsCx<T>*)(lds + (-1 - h)) + o_begin; };
-#define KN_RUN(A, B, C) \
-  return step_outputs<T>(A(ha), B(hb), C(hc), ix, nm, nn, k0, nk, o_begin, o_end, scale, L, tid, nthr)
-  if (ha < 0) {
-    if (hb < 0) {
-      if (hc < 0) KN_RUN(ld, ld, ldo);
-      KN_RUN(ld, ld, glo);
-    }
-    if (hc < 0) KN_RUN(ld, gl, ldo);
-    KN_RUN(ld, gl, glo);
-  }
-  if (hb < 0) {
-    if (hc < 0) KN_RUN(gl, ld, ldo);
-    KN_RUN(gl, ld, glo);
-  }
-  if (hc < 0) KN_RUN(gl, gl, ldo);
-  KN_RUN(gl, gl, glo);
-#undef KN_RUN
 }
 
 template <class T>
@@ -635,86 +496,300 @@ __device__ inline T step_scale(const States& st, int32_t a, int32_t b, int64_t& 
   return (T)ldexp(1.0, -sh);
 }
 
-__device__ inline int32_t step_tab_entries(const StepDesc& d) {
-  return 2 * d.nb + d.nm + 2 * d.nk + d.nn;
-}
-
-template <class T>
-__device__ inline Cx<T>* home_ptr(int32_t home, Cx<T>* arena, Cx<T>* lds) {
-  return home >= 0 ? arena + home : lds + (-1 - home);
-}
-
-// One serial step C = A . B on threads tid = 0..nthr-1, with the gather
-// tables `tab` (A_b A_m A_k B_b B_k B_n, generated in LDS) and the states of
-// operands made before the task in ext[0..1].  Returns this thread's max |.|
-// and C's exponent.
+// ---- serial runs
 //
-// A step the whole workgroup computes (nthr = kBlock) first copies operands
-// that live in the global arena into the staging area (entries stage_off ..
-// stage_off + stage_elems - 1 of the LDS arena pointer), A first, each when it
-// fits: one burst of independent coalesced loads, after which the step's
-// gathers read LDS.  The products and their order are unchanged.
+// The steps of a serial task are small (a few tens of outputs, a contracted
+// extent of 3 or 9), so what bounds a run is the latency of each step's chain
+// of some hundreds of dependent instructions, and how many steps run at once,
+// not products or memory.  Hence:
+//   - no gather tables: an entry's offsets in A and B are decoded from its
+//     index digit by digit, the strides of each digit held in LDS.  Tables of
+//     the offsets were generated entry by entry before a run and cost a quarter
+//     of its time;
+//   - the outputs of a dependency level, step after step, are shared out to the
+//     wavefronts 64 at a time, each lane with the step of its output: a level
+//     of 64 steps of 9 to 27 outputs takes each wavefront three rounds, not
+//     the eight steps one after another that it took a wavefront per step;
+//   - only a level ends with a barrier: an output's shift is the maximum over
+//     its entries, kept by an LDS atomic.
+// Steps with a long contracted index (more than two spins) run as units: 2^l
+// lanes share an output, and units of up to about kUnitMacs multiply-adds are
+// taken by the wavefronts in turn.
+// Figures: the launch of one 600-crossing knot (q = 3, complex128) 480 -> 218 us,
+// of one 250-crossing knot with q = 5 170 -> 108 us, of gradients of 8 knots
+// 700 -> 300 us, all with the LDS arena of 96 KiB.
+constexpr int32_t kUnitMacs = 1024;
+constexpr float kStageMacs = 4096.0f;
+constexpr int32_t kDigCap = kTabBuf / 2;  // digit strides (pairs) of a chunk
+static_assert(kDescBuf == 64, "lane j holds step j of a chunk");
+
+// A flat step as its lanes read it from LDS.
+struct alignas(16) FlatRec {
+  int32_t o_start;     // its first output among those of the chunk's flat steps
+  int32_t i_start;     // its first item (q outputs) among theirs
+  int32_t dig_off;     // its digit strides
+  int32_t R, o_step;   // output digits; outputs per value of the highest one
+  int32_t q0, q1;      // values of the lowest contracted digit and of the one above (1: none)
+  int32_t ha, hb, hc;  // homes
+  int32_t ia, ib, ic;  // states of A, B and C in the state arrays
+};
+static_assert(sizeof(FlatRec) == kFlatRecBytes, "LDS layout");
+
+// A unit: a run of one step's outputs (uniform over the wavefront).
 template <class T>
-__device__ inline T serial_step(const StepDesc& d, const int32_t* tab, Cx<T>* arena, Cx<T>* lds,
-                                const States& st, const TensorState* ext, int32_t tid,
-                                int32_t nthr, int32_t stage_off, int32_t stage_elems,
-                                int64_t& ec) {
-  TabIx ix;
-  ix.ab = tab;
-  ix.am = ix.ab + d.nb;
-  ix.ak = ix.am + d.nm;
-  ix.bb = ix.ak + d.nk;
-  ix.bk = ix.bb + d.nb;
-  ix.bn = ix.bk + d.nk;
-  int32_t sa, sb;
-  int64_t ea, eb;
-  if (st.local(d.a)) st.get(d.a, sa, ea);
-  else { sa = ext[0].shift; ea = ext[0].exp2; }
-  if (st.local(d.b)) st.get(d.b, sb, eb);
-  else { sb = ext[1].shift; eb = ext[1].exp2; }
-  const int32_t sh = shift_of(sa) + shift_of(sb);
-  ec = ea + eb + sh;
-  const T scale = (T)ldexp(1.0, -sh);
-  const int64_t outs = (int64_t)d.nb * d.nm * d.nn;
-  const int32_t L = lanes_per_output(outs, d.nk, nthr);
-  int32_t ha = d.home_a, hb = d.home_b;
-  if (nthr == kBlock && (ha >= 0 || hb >= 0)) {
-    // sizes of A (spins b, m, k) and B (spins b, k, n)
-    const int64_t na = (int64_t)d.nb * d.nm * d.nk, nbb = (int64_t)d.nb * d.nk * d.nn;
-    const bool sa = ha >= 0 && na <= stage_elems;
-    const int64_t used = sa ? na : 0;
-    const bool sb = hb >= 0 && used + nbb <= stage_elems;
-    if (sa || sb) {
-      LdsCx<T>* stg = (LdsCx<T>*)(lds + stage_off);
-      if (sa) {
-        const GlbCx<T>* g = (const GlbCx<T>*)(arena + ha);
-        for (int32_t i = tid; i < (int32_t)na; i += kBlock) put(stg, i, ldc(g + i));
-        ha = -1 - stage_off;
+struct UnitCtx {
+  int2 dig;            // lane d: strides in A and B of output digit d, then of
+                       // contracted digits from lane R, least significant first
+  int32_t R, rk, q;    // output digits, contracted digits
+  int32_t nkq, qi;     // contracted extent = nkq values of its upper digits x qi
+  int32_t log_l;       // lanes per output
+  int32_t o0, o1;      // outputs of this unit
+  int32_t ha, hb, hc;  // homes of A, B and C
+  bool small;          // every index is below kSmallIndex
+  uint32_t m18;
+  T scale;
+  QDiv D;
+};
+
+// Offsets in A and B of index x < q^n over n digits from d0.  Four digits at a
+// time without a branch: a taken branch costs a lone wavefront as much as
+// several digits, and the digits past the last are zero.
+template <class T>
+__device__ inline int2 unit_offsets(const UnitCtx<T>& u, int32_t x, int32_t d0, int32_t n) {
+  int2 off{0, 0};
+  if (u.small) {
+    for (int32_t d = d0; d < d0 + n; d += 4) {
+#pragma unroll
+      for (int32_t i = 0; i < 4; ++i) {
+        const uint32_t up = __umul24((uint32_t)x, u.m18) >> 18;
+        const uint32_t r = (uint32_t)x - __umul24(up, (uint32_t)u.q);
+        off.x += (int32_t)__umul24(r, (uint32_t)rl(u.dig.x, d + i));
+        off.y += (int32_t)__umul24(r, (uint32_t)rl(u.dig.y, d + i));
+        x = (int32_t)up;
       }
-      if (sb) {
-        const GlbCx<T>* g = (const GlbCx<T>*)(arena + hb);
-        for (int32_t i = tid; i < (int32_t)nbb; i += kBlock) put(stg + used, i, ldc(g + i));
-        hb = -1 - (stage_off + (int32_t)used);
-      }
-      __syncthreads();
+    }
+  } else {
+    for (int32_t d = d0; d < d0 + n; ++d) {
+      const int32_t up = u.D.div(x);
+      const int32_t r = x - up * u.q;
+      off.x += r * rl(u.dig.x, d);
+      off.y += r * rl(u.dig.y, d);
+      x = up;
     }
   }
-  return step_outputs_homes<T>(ha, hb, d.home_c, arena, lds, ix, d.nm, d.nn, 0, d.nk, 0, outs,
-                               scale, L, tid, nthr);
+  return off;
 }
 
-// Serial steps [first, first + count): descriptors are staged in LDS one
-// chunk at a time and the chunk's gather tables are generated there from the
-// strides; the chunk then runs with no global round trip except operands that
-// live in the global arena.
-// Serial steps of a level with fewer products than this run on one wavefront.
-constexpr int64_t kWaveMacs = 2048;
+// The high word of |v|: its exponent field orders magnitudes by power of two.
+__device__ inline uint32_t mag_word(double v) {
+  return (uint32_t)(__builtin_bit_cast(uint64_t, v) >> 32) & 0x7fffffffu;
+}
+__device__ inline uint32_t mag_word(float v) { return __builtin_bit_cast(uint32_t, v) & 0x7fffffffu; }
+// frexp exponent of the largest magnitude with that word (kShiftNone for
+// zeros and subnormals, 0 for infinities and NaN).
+template <class T>
+__device__ inline int32_t mag_shift(uint32_t w) {
+  constexpr int32_t kBits = sizeof(T) == 8 ? 20 : 23, kMax = sizeof(T) == 8 ? 2047 : 255;
+  const int32_t e = (int32_t)(w >> kBits);
+  return e == 0 ? kShiftNone : e == kMax ? 0 : e - (kMax / 2 - 1);
+}
 
 template <class T>
+__device__ inline void cfma(Cx<T>& c, Cx<T> a, Cx<T> b) {
+  c.re = fma(a.re, b.re, c.re);
+  c.im = fma(a.re, b.im, c.im);
+  c.re = fma(-a.im, b.im, c.re);
+  c.im = fma(a.im, b.re, c.im);
+}
+
+// N entries of an operand from entry `off` of the arena it lives in (home < 0:
+// LDS), `stride` apart.  The branch is uniform; each side keeps its own address
+// space (a generic load would wait for every earlier store), and one copy of
+// the code around it serves all four combinations of homes: a run's code is
+// fetched anew in every launch, and four copies of it were a good part of the
+// time of a single small knot.
+template <int N, class T>
+__device__ inline void load_entries(Cx<T>* arena, Cx<T>* lds, int32_t home, int32_t off, int32_t stride,
+                                    Cx<T> (&v)[N]) {
+  if (home < 0) {
+    const LdsCx<T>* p = (const LdsCx<T>*)(lds + (-1 - home)) + off;
+#pragma unroll
+    for (int j = 0; j < N; ++j) v[j] = ldc(p + j * stride);
+  } else {
+    const GlbCx<T>* p = (const GlbCx<T>*)(arena + home) + off;
+#pragma unroll
+    for (int j = 0; j < N; ++j) v[j] = ldc(p + j * stride);
+  }
+}
+
+// NO outputs per lane (base + slot, and base + slot + one round): the loads
+// of three contracted entries of all of them are issued before their products.
+// 2^log_l lanes share an output's contracted entries.  Returns the largest
+// mag_word stored by this lane.
+template <int NO, class T>
+__device__ __attribute__((always_inline)) uint32_t unit_round(const UnitCtx<T>& u, Cx<T>* arena, Cx<T>* lds,
+                                                               int32_t base, int32_t lane) {
+  const int32_t lsub = lane & ((1 << u.log_l) - 1);
+  const int32_t nslot = 64 >> u.log_l;
+  const int32_t o = base + (lane >> u.log_l);
+  const int32_t a0 = rl(u.dig.x, u.R), b0 = rl(u.dig.y, u.R);
+  int2 f[NO];
+  Cx<T> c[NO];
+#pragma unroll
+  for (int i = 0; i < NO; ++i) {
+    // (lanes past the end repeat the last output and store nothing)
+    f[i] = unit_offsets(u, min(o + i * nslot, u.o1 - 1), 0, u.R);
+    c[i] = Cx<T>{0, 0};
+  }
+  for (int32_t kk = lsub; kk < u.nkq; kk += 1 << u.log_l) {
+    const int2 kf = u.nkq > 1 ? unit_offsets(u, kk, u.R + 1, u.rk - 1) : int2{0, 0};
+    // the entries of the lowest contracted digit at value kk of the others
+    int32_t d = 0;
+#pragma unroll 1
+    for (; d + 3 <= u.qi; d += 3) {
+      Cx<T> va[NO][3], vb[NO][3];
+#pragma unroll
+      for (int i = 0; i < NO; ++i) {
+        load_entries<3>(arena, lds, u.ha, f[i].x + kf.x + d * a0, a0, va[i]);
+        load_entries<3>(arena, lds, u.hb, f[i].y + kf.y + d * b0, b0, vb[i]);
+      }
+#pragma unroll
+      for (int j = 0; j < 3; ++j)
+#pragma unroll
+        for (int i = 0; i < NO; ++i) cfma(c[i], va[i][j], vb[i][j]);
+    }
+#pragma unroll 1
+    for (; d < u.qi; ++d) {
+      Cx<T> va[NO][1], vb[NO][1];
+#pragma unroll
+      for (int i = 0; i < NO; ++i) {
+        load_entries<1>(arena, lds, u.ha, f[i].x + kf.x + d * a0, 0, va[i]);
+        load_entries<1>(arena, lds, u.hb, f[i].y + kf.y + d * b0, 0, vb[i]);
+      }
+#pragma unroll
+      for (int i = 0; i < NO; ++i) cfma(c[i], va[i][0], vb[i][0]);
+    }
+  }
+  for (int32_t m = (1 << u.log_l) >> 1; m >= 1; m >>= 1) {
+#pragma unroll
+    for (int i = 0; i < NO; ++i) {
+      c[i].re += __shfl_xor(c[i].re, m, 64);
+      c[i].im += __shfl_xor(c[i].im, m, 64);
+    }
+  }
+  uint32_t top = 0;
+#pragma unroll
+  for (int i = 0; i < NO; ++i) {
+    const int32_t oi = o + i * nslot;
+    if (lsub == 0 && oi < u.o1) {
+      c[i].re *= u.scale;
+      c[i].im *= u.scale;
+      if (u.hc >= 0) put(GlbOut<T>((GlbCx<T>*)(arena + u.hc) + u.o0), oi - u.o0, c[i]);
+      else put((LdsCx<T>*)(lds + (-1 - u.hc)), oi, c[i]);
+      top = max(top, max(mag_word(c[i].re), mag_word(c[i].im)));
+    }
+  }
+  return top;
+}
+
+// One item of a flat step: outputs o + t q^(R - 1) for t < T, in step `r` of
+// the lane.  F says where the operands of all the lanes are: 0 LDS, 1 the global
+// arena, 2 either (generic loads, which wait for earlier stores too).
+template <int F, class T>
+__device__ inline void flat_item(const FlatRec& r, const int2* s_dig, int32_t o, int32_t n_t, uint32_t q,
+                                 uint32_t m18, Cx<T>* arena, Cx<T>* lds, const States& st, bool write) {
+  const int2* dg = s_dig + r.dig_off;
+  int32_t fa = 0, fb = 0;
+  uint32_t x = (uint32_t)o;
+  // (the digits past the last are zero)
+  for (int32_t d = 0; __any(d < r.R); d += 4) {
+    int2 s4[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) s4[i] = dg[min(d + i, r.R)];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t up = __umul24(x, m18) >> 18;
+      const uint32_t v = x - __umul24(up, q);
+      fa += (int32_t)__umul24(v, (uint32_t)s4[i].x);
+      fb += (int32_t)__umul24(v, (uint32_t)s4[i].y);
+      x = up;
+    }
+  }
+  // strides of the contracted digits (past them: other steps', not used) and
+  // of the highest output digit
+  const int2 s0 = dg[r.R], s1 = dg[r.R + 1], top = dg[max(r.R - 1, 0)];
+  const int32_t o_step = r.o_step;
+  const int32_t sh = shift_of(st.sh[r.ia]) + shift_of(st.sh[r.ib]);
+  const T scale = (T)ldexp(1.0, -sh);
+  uint32_t mag = 0;
+  auto run = [&](auto pa, auto pb) {
+    for (int32_t t = 0; t < n_t; t += 3) {
+      Cx<T> c[3] = {{0, 0}, {0, 0}, {0, 0}};
+      auto pa1 = pa;
+      auto pb1 = pb;
+      for (int32_t k1 = 0; k1 < r.q1; ++k1) {
+        for (int32_t k0 = 0; k0 < r.q0; k0 += 3) {
+          Cx<T> va[3][3], vb[3][3];
+#pragma unroll
+          for (int k = 0; k < 3; ++k)
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+              va[k][j] = vb[k][j] = Cx<T>{0, 0};
+              if (t + j < n_t && k0 + k < r.q0) {
+                va[k][j] = ldc(pa1 + ((k0 + k) * s0.x + j * top.x));
+                vb[k][j] = ldc(pb1 + ((k0 + k) * s0.y + j * top.y));
+              }
+            }
+#pragma unroll
+          for (int k = 0; k < 3; ++k)
+#pragma unroll
+            for (int j = 0; j < 3; ++j) cfma(c[j], va[k][j], vb[k][j]);
+        }
+        pa1 += s1.x;
+        pb1 += s1.y;
+      }
+      pa += 3 * top.x;
+      pb += 3 * top.y;
+#pragma unroll
+      for (int j = 0; j < 3; ++j) {
+        if (write && t + j < n_t) {
+          c[j].re *= scale;
+          c[j].im *= scale;
+          const int32_t oj = o + (t + j) * o_step;
+          if (r.hc < 0) put((LdsCx<T>*)(lds + (-1 - r.hc)), oj, c[j]);
+          else put_through(arena + r.hc + oj, c[j]);
+          mag = max(mag, max(mag_word(c[j].re), mag_word(c[j].im)));
+        }
+      }
+    }
+  };
+  if constexpr (F == 0)
+    run((const LdsCx<T>*)(lds + (-1 - r.ha)) + fa, (const LdsCx<T>*)(lds + (-1 - r.hb)) + fb);
+  else if constexpr (F == 1)
+    run((const GlbCx<T>*)(arena + r.ha) + fa, (const GlbCx<T>*)(arena + r.hb) + fb);
+  else
+    run((const Cx<T>*)(r.ha < 0 ? lds + (-1 - r.ha) : arena + r.ha) + fa,
+        (const Cx<T>*)(r.hb < 0 ? lds + (-1 - r.hb) : arena + r.hb) + fb);
+  if (write) {
+    __hip_atomic_fetch_max((__attribute__((address_space(3))) int32_t*)&st.sh[r.ic], mag_shift<T>(mag),
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    if (o == 0) st.ex[r.ic] = st.ex[r.ia] + st.ex[r.ib] + sh;
+  }
+}
+
+// Serial steps [first, first + count).
+//
+// A larger step first has its operands that live in the global arena
+// copied to the staging area after the LDS arena (A first, each when it fits):
+// one burst of independent coalesced loads by the whole workgroup, after which
+// the step's gathers read LDS.
+template <class T>
 __device__ __attribute__((always_inline)) void serial_steps(const DevProg& p, int32_t first, int32_t count, int32_t q,
-                             Cx<T>* arena, Cx<T>* lds, int32_t* s_tab, StepDesc* s_desc,
-                             int32_t* s_tb, TensorState* s_ext, const States& st, T* s_red,
-                             int64_t* ph) {
+                             Cx<T>* arena, Cx<T>* lds, int2* s_dig, FlatRec* s_rec,
+                             const States& st, int32_t made, int64_t* ph) {
+  const int32_t tid = task_tid();
+  const int32_t lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  constexpr int32_t kWaves = kBlock / 64;
   int64_t tk = ph ? wall_clock64() : 0;
   auto lap = [&](int i) {
     if (ph) {
@@ -723,111 +798,238 @@ __device__ __attribute__((always_inline)) void serial_steps(const DevProg& p, in
       tk = t;
     }
   };
-  const int32_t tid = task_tid();
-  constexpr int32_t kDescWords = (int32_t)(sizeof(StepDesc) / 4);
-  const QDiv D(q);
+  const QDiv D = qdiv_of(q);
   // the staging area follows the tensor arena
   const int32_t stage_off = p.h->lds_bytes / (int32_t)sizeof(Cx<T>);
   const int32_t stage_elems = stage_bytes(p.h->lds_bytes) / (int32_t)sizeof(Cx<T>);
-  int32_t s = first;
   const int32_t end = first + count;
-  while (s < end) {
-    const int32_t nd = min(end - s, kDescBuf);
-    {
-      const int32_t* src = reinterpret_cast<const int32_t*>(p.steps + s);
-      int32_t* dst = reinterpret_cast<int32_t*>(s_desc);
-      for (int32_t i = tid; i < nd * kDescWords; i += kBlock) dst[i] = src[i];
+  const uint32_t m18 = small_magic(q);
+  int32_t ce = 0;
+  StepDesc next{};
+  if (first + lane < end) next = p.steps[first + lane];
+  for (int32_t s = first; s < end; s += ce) {
+    // lane j: step s + j (loaded while the chunk before it ran)
+    const bool have = s + lane < end;
+    const StepDesc d = next;
+    const int32_t rb = d.ranks & 255, rm = (d.ranks >> 8) & 255, rk = (d.ranks >> 16) & 255,
+                  rn = (d.ranks >> 24) & 255;
+    const int32_t R = rb + rm + rn;
+    const int32_t n_dig = have ? R + rk : 0;
+    const int32_t dig_end = wave_scan(n_dig);
+    // the steps whose digits fit (a step has at most 62)
+    const uint64_t fits = __ballot(have && dig_end <= kDigCap);
+    ce = __popcll(fits);
+    const int32_t dig_off = dig_end - n_dig;
+    const int32_t outs = d.nb * d.nm * d.nn;
+    // units: runs of whole wavefronts of outputs
+    int32_t run = max(outs, 1), units = 0;
+    const int32_t nkq = rk > 0 ? D.div(d.nk) : 1;
+    int32_t log_l = 0;
+    // lanes per output: to fill a wavefront, and the workgroup where the
+    // contracted index is long enough to be worth a reduction over lanes
+    while (log_l < 6 && (2 << log_l) <= nkq &&
+           ((int64_t)outs << log_l) < (d.nk >> log_l >= 16 ? kBlock : 64))
+      ++log_l;
+    const int32_t pack = R | rk << 8 | log_l << 16 | (outs <= kSmallIndex && nkq <= kSmallIndex ? 1 << 24 : 0);
+    // flat: at most two contracted spins, and every state in LDS
+    auto made_here = [&](int32_t t) { return (uint32_t)(t - st.lo) < (uint32_t)made; };
+    auto in_lds = [&](int32_t t) { return st.local(t) || !made_here(t); };
+    const bool flat = lane < ce && rk <= 2 && outs <= kSmallIndex && in_lds(d.a) && in_lds(d.b) && st.local(d.c);
+    const int32_t o_step = R > 0 ? D.div(outs) : 1;
+    const int32_t f_end = wave_scan(flat ? outs : 0), i_end = wave_scan(flat ? o_step : 0);
+    if (wv == 0 && flat) {
+      FlatRec r;
+      r.o_start = f_end - outs;
+      r.i_start = i_end - o_step;
+      r.o_step = o_step;
+      r.dig_off = dig_off;
+      r.R = R;
+      r.q0 = rk > 0 ? q : 1;
+      r.q1 = rk > 1 ? q : 1;
+      r.ha = d.home_a;
+      r.hb = d.home_b;
+      r.hc = d.home_c;
+      r.ia = st.local(d.a) ? d.a - st.lo : kStateCap + 2 * lane;
+      r.ib = st.local(d.b) ? d.b - st.lo : kStateCap + 2 * lane + 1;
+      r.ic = d.c - st.lo;
+      s_rec[lane] = r;
     }
-    __syncthreads();
-    // steps of this chunk: as many as fit the table buffer (at least one)
-    int32_t ce = 0, tab_end = 0;
-    for (int32_t j = 0; j < nd; ++j) {
-      const int32_t e = tab_end + step_tab_entries(s_desc[j]);
-      if (e > kTabBuf) break;
-      if (tid == 0) s_tb[j] = tab_end;
-      ce = j + 1;
-      tab_end = e;
+    if (lane < ce && !flat) {
+      const float macs = (float)outs * (float)d.nk;
+      const int32_t wide = 64 >> log_l;  // outputs of a wavefront
+      const int32_t want = (int32_t)fminf(macs * (1.0f / kUnitMacs), (float)((outs + wide - 1) / wide));
+      if (want > 1) run = ((outs + want - 1) / want + wide - 1) & -wide;
+      units = (outs + run - 1) / run;
     }
-    if (tid == 0) s_tb[ce] = tab_end;
-    // states of operands made before this task (already final) are fetched now
-    if (tid < 2 * ce) {
-      const int32_t j = tid >> 1;
-      const int32_t t = (tid & 1) ? s_desc[j].b : s_desc[j].a;
-      if (!st.local(t)) s_ext[tid] = p.ts[t];
-    }
-    __syncthreads();
-    // generate the gather tables: entry i belongs to step j (binary search)
-    for (int32_t i = tid; i < tab_end; i += kBlock) {
-      int32_t lo = 0, hi = ce - 1;
-      while (lo < hi) {
-        const int32_t mid = (lo + hi + 1) >> 1;
-        if (s_tb[mid] <= i) lo = mid;
-        else hi = mid - 1;
+    const bool large = lane < ce && d.nk > 1 && (flat ? (float)outs * (float)d.nk >= kStageMacs : units > 1);
+    const int32_t u_sum = wave_scan(units);
+    const int32_t u_end = lane < ce ? u_sum : INT32_MAX;
+    const int32_t prev_lvl = __shfl_up(d.lvl, 1, 64);
+    uint64_t starts = __ballot(lane < ce && (lane == 0 || d.lvl != prev_lvl));
+    // states of operands made before this task (final) are fetched now; those
+    // of tensors it makes itself are in LDS (or, past what LDS holds, global)
+    if (wv < 2 && lane < ce) {
+      const int32_t t = wv ? d.b : d.a;
+      if (!made_here(t)) {
+        const TensorState x = p.ts[t];
+        st.sh[kStateCap + 2 * lane + wv] = x.shift;
+        st.ex[kStateCap + 2 * lane + wv] = x.exp2;
       }
-      const StepDesc& d = s_desc[lo];
-      int32_t r = i - s_tb[lo];
-      const int32_t rb = d.ranks & 255, rm = (d.ranks >> 8) & 255, rk = (d.ranks >> 16) & 255,
-                    rn = (d.ranks >> 24) & 255;
-      const int32_t* sp = p.strides + d.str;
-      int32_t off;
-      if (r < d.nb) {
-        off = group_off(r, sp, rb, D);
-      } else if ((r -= d.nb) < d.nm) {
-        off = group_off(r, sp + rb, rm, D);
-      } else if ((r -= d.nm) < d.nk) {
-        off = group_off(r, sp + rb + rm, rk, D);
-      } else if ((r -= d.nk) < d.nb) {
-        off = group_off(r, sp + rb + rm + rk, rb, D);
-      } else if ((r -= d.nb) < d.nk) {
-        off = group_off(r, sp + 2 * rb + rm + rk, rk, D);
+    }
+    // digit strides: entry i belongs to step j (the steps whose digits end
+    // before it, counted by bisection over the lanes)
+    const int32_t n_ent = rl(dig_end, ce - 1);
+    for (int32_t i = tid; i < ((n_ent + 63) & ~63); i += kBlock) {
+      int32_t j = 0;
+#pragma unroll
+      for (int32_t h = 32; h >= 1; h >>= 1)
+        if (__shfl(dig_end, j + h - 1, 64) <= i) j += h;
+      const int32_t jr = __shfl(d.ranks, j, 64), jo = __shfl(dig_off, j, 64), js = __shfl(d.str, j, 64);
+      const int32_t b = jr & 255, m = (jr >> 8) & 255, k = (jr >> 16) & 255, n = (jr >> 24) & 255;
+      int32_t x = i - jo;
+      // strides: A_b A_m A_k B_b B_k B_n, most significant spin first
+      int32_t ia = -1, ib = -1;
+      if (x < n) {
+        ib = 2 * b + m + 2 * k + n - 1 - x;
+      } else if ((x -= n) < m) {
+        ia = b + m - 1 - x;
+      } else if ((x -= m) < b) {
+        ia = b - 1 - x;
+        ib = b + m + k + b - 1 - x;
       } else {
-        r -= d.nk;
-        off = group_off(r, sp + 2 * rb + rm + 2 * rk, rn, D);
+        x -= b;
+        ia = b + m + k - 1 - x;
+        ib = 2 * b + m + 2 * k - 1 - x;
       }
-      s_tab[i] = off;
+      if (i < n_ent) {
+        const int32_t* sp = p.strides + js;
+        s_dig[i] = int2{ia >= 0 ? sp[ia] : 0, ib >= 0 ? sp[ib] : 0};
+      }
     }
+    next = StepDesc{};
+    if (s + ce + lane < end) next = p.steps[s + ce + lane];
     __syncthreads();
     lap(1);
-    // levels: a run of adjacent steps of equal level is independent; a lone
-    // step uses the whole workgroup, otherwise each wavefront takes steps of
-    // the level in turn, and one barrier ends the level
-    for (int32_t j = 0; j < ce;) {
-      int32_t je = j + 1;
-      while (je < ce && s_desc[je].lvl == s_desc[j].lvl) ++je;
-      // steps with many products use the whole workgroup, one after another;
-      // the rest are shared out to the wavefronts
-      for (int32_t u = j; u < je; ++u) {
-        const StepDesc& d = s_desc[u];
-        if (je - j > 1 && (int64_t)d.nb * d.nm * d.nn * d.nk < kWaveMacs) continue;
-        int64_t ec;
-        T lm = serial_step<T>(d, s_tab + s_tb[u], arena, lds, st, s_ext + 2 * u,
-                              tid, kBlock, stage_off, stage_elems, ec);
-        lm = block_max<T>(lm, s_red);
-        if (tid == 0) st.set(d.c, frexp_shift<T>(lm), ec);
+    int32_t ha = d.home_a, hb = d.home_b;
+    while (starts) {
+      const int32_t j0 = __ffsll((unsigned long long)starts) - 1;
+      starts &= starts - 1;
+      const int32_t j1 = starts ? __ffsll((unsigned long long)starts) - 1 : ce;
+      // larger steps with operands in the global arena
+      uint64_t stage = __ballot(lane >= j0 && lane < j1 && large && (ha >= 0 || hb >= 0));
+      if (stage) {
+        LdsCx<T>* stg = (LdsCx<T>*)(lds + stage_off);
+        int32_t used = 0;
+        do {
+          const int32_t j = __ffsll((unsigned long long)stage) - 1;
+          stage &= stage - 1;
+          const int32_t bk = rl(d.nb, j) * rl(d.nk, j);
+#pragma unroll
+          for (int op = 0; op < 2; ++op) {
+            const int32_t h = op ? rl(hb, j) : rl(ha, j);
+            if (h < 0) continue;
+            const int64_t n = (int64_t)bk * (op ? rl(d.nn, j) : rl(d.nm, j));
+            if (n > stage_elems - used) continue;
+            const GlbCx<T>* src = (const GlbCx<T>*)(arena + h);
+            for (int32_t i = tid; i < (int32_t)n; i += kBlock) put(stg + used, i, ldc(src + i));
+            const int32_t home = -1 - (stage_off + used);
+            if (op) hb = lane == j ? home : hb;
+            else ha = lane == j ? home : ha;
+            if (tid == 0) (op ? s_rec[j].hb : s_rec[j].ha) = home;
+            used += (int32_t)n;
+          }
+        } while (stage);
+        __syncthreads();
       }
-      if (je - j > 1) {
-        // the wavefront index is uniform within a wavefront: readfirstlane
-        // lets the step's descriptor live in scalar registers
-        const int32_t wv = __builtin_amdgcn_readfirstlane((int32_t)(tid >> 6));
-        const int32_t lane = tid & 63;
-        int32_t r = 0;  // rank among the level's small steps
-        for (int32_t u = j; u < je; ++u) {
-          const StepDesc& d = s_desc[u];
-          if ((int64_t)d.nb * d.nm * d.nn * d.nk >= kWaveMacs) continue;
-          if ((r++ & (kBlock / 64 - 1)) != wv) continue;
-          int64_t ec;
-          T lm = serial_step<T>(d, s_tab + s_tb[u], arena, lds, st, s_ext + 2 * u, lane, 64, 0, 0,
-                                ec);
-          lm = wave_max(lm);
-          if (lane == 0) st.set(d.c, frexp_shift<T>(lm), ec);
+      // flat steps: a lane takes the q outputs that differ in the highest
+      // digit (their offsets are decoded once), or, where a level has no more
+      // outputs than the workgroup has lanes, a single one
+      const int32_t of0 = j0 ? rl(f_end, j0 - 1) : 0, of1 = rl(f_end, j1 - 1);
+      const bool single = of1 - of0 <= kBlock;
+      const int32_t l_end = single ? f_end : i_end;
+      const int32_t x1 = single ? of1 : rl(i_end, j1 - 1);
+      for (int32_t x0 = (single ? of0 : j0 ? rl(i_end, j0 - 1) : 0) + 64 * wv; x0 < x1; x0 += kBlock) {
+        const int32_t x = min(x0 + lane, x1 - 1);
+        const FlatRec r = s_rec[lane_of(l_end, x, j0, j1)];
+        const int32_t o = x - (single ? r.o_start : r.i_start);
+        const int32_t n_t = single || r.R == 0 ? 1 : q;
+        const bool write = x0 + lane < x1;
+        if (!__any(r.ha >= 0 || r.hb >= 0))
+          flat_item<0, T>(r, s_dig, o, n_t, (uint32_t)q, m18, arena, lds, st, write);
+        else if (!__any(r.ha < 0 || r.hb < 0))
+          flat_item<1, T>(r, s_dig, o, n_t, (uint32_t)q, m18, arena, lds, st, write);
+        else
+          flat_item<2, T>(r, s_dig, o, n_t, (uint32_t)q, m18, arena, lds, st, write);
+      }
+      const int32_t u0 = j0 ? rl(u_end, j0 - 1) : 0, u1 = rl(u_end, j1 - 1);
+      if (u0 < u1) {
+        // lane j: the scale 2^-sh of step j; its output's exponent
+        int32_t sh = 0;
+        if (lane >= j0 && lane < j1 && !flat) {
+          int32_t sa, sb;
+          int64_t ea, eb;
+          auto state = [&](int32_t t, int32_t e, int32_t& shift, int64_t& ex) {
+            if (st.local(t) || !made_here(t)) {
+              const int32_t i = st.local(t) ? t - st.lo : kStateCap + e;
+              shift = st.sh[i];
+              ex = st.ex[i];
+            } else {
+              st.get_late(t, shift, ex);
+            }
+          };
+          state(d.a, 2 * lane, sa, ea);
+          state(d.b, 2 * lane + 1, sb, eb);
+          sh = shift_of(sa) + shift_of(sb);
+          if (wv == 0) {
+            if (st.local(d.c)) st.ex[d.c - st.lo] = ea + eb + sh;
+            else
+              __hip_atomic_store(&st.g[d.c].exp2, ea + eb + sh, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          }
+        }
+        // the digit strides of a wavefront's next unit are loaded while it
+        // computes the one before
+        auto step_of = [&](int32_t x) { return (int32_t)__popcll(__ballot(u_end <= x)); };
+        auto digits_of = [&](int32_t j) {
+          return s_dig[rl(dig_off, j) + min(lane, max((rl(pack, j) & 255) + ((rl(pack, j) >> 8) & 255) - 1, 0))];
+        };
+        int32_t x = u0 + wv;
+        int32_t j = min(step_of(x), ce - 1);
+        int2 dig_next = digits_of(j);
+        for (; x < u1; x += kWaves) {
+          const int2 dig = dig_next;
+          const int32_t j_next = min(step_of(x + kWaves), ce - 1);
+          dig_next = digits_of(j_next);
+          const int32_t part = x - (j ? rl(u_end, j - 1) : 0);
+          const int32_t pk = rl(pack, j);
+          const int32_t uR = pk & 255, urk = (pk >> 8) & 255;
+          const int32_t len = rl(run, j);
+          const UnitCtx<T> u{dig, uR, urk, q, rl(nkq, j), urk > 0 ? q : 1, (pk >> 16) & 255, part * len,
+                             min(rl(outs, j), part * len + len), rl(ha, j), rl(hb, j), rl(d.home_c, j),
+                             (pk >> 24) != 0, m18,
+                             (T)ldexp(1.0, -rl(sh, j)), D};
+          const int32_t nslot = 64 >> u.log_l;
+          uint32_t top = 0;
+          int32_t at = u.o0;
+  #pragma unroll 1
+          for (; at + nslot < u.o1; at += 2 * nslot) top = max(top, unit_round<2>(u, arena, lds, at, lane));
+          if (at < u.o1) top = max(top, unit_round<1>(u, arena, lds, at, lane));
+          const int32_t mx = wave_max_last((int32_t)top);
+          if (lane == 63) {
+            const int32_t tc = rl(d.c, j);
+            if (st.local(tc))
+              __hip_atomic_fetch_max((__attribute__((address_space(3))) int32_t*)&st.sh[tc - st.lo],
+                                     mag_shift<T>((uint32_t)mx), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            else
+              __hip_atomic_fetch_max(&st.g[tc].shift, mag_shift<T>((uint32_t)mx), __ATOMIC_RELAXED,
+                                     __HIP_MEMORY_SCOPE_AGENT);
+          }
+          j = j_next;
         }
       }
       lap(2);
       __syncthreads();
       lap(3);
-      j = je;
     }
-    s += ce;
   }
 }
 
@@ -845,62 +1047,135 @@ __device__ inline void tile_publish(const DevProg& p, int32_t c, int32_t tile_id
   }
 }
 
-// Offset tables of the six spin groups of step s (A_b A_m A_k B_b B_k B_n).
-__device__ inline GenIx step_ix(const DevProg& p, const StepDesc& s, int32_t q) {
-  const int32_t rb = s.ranks & 255, rm = (s.ranks >> 8) & 255, rk = (s.ranks >> 16) & 255,
-                rn = (s.ranks >> 24) & 255;
-  const int32_t* sp = p.strides + s.str;
-  return GenIx{{nullptr, nullptr, nullptr, nullptr, nullptr, nullptr},
-               {sp, sp + rb, sp + rb + rm, sp + rb + rm + rk, sp + 2 * rb + rm + rk,
-                sp + 2 * rb + rm + 2 * rk},
-               {rb, rm, rk, rb, rk, rn},
-               0,
-               QDiv(q)};
+// Offsets in A and B of an index over a list of spins, in LDS: one entry per
+// value of the lowest spins (together `n_lo` values) and one per value of the
+// rest that a task meets, added up on use.  Few enough of either to be made in
+// a round or two by the workgroup whatever the index's range: one table of the
+// whole range seldom fits LDS for a wide step, whose offsets were then decoded
+// spin by spin, from strides in global memory, at every use.
+struct SplitTab {
+  const int2* lo;
+  const int2* hi;   // of value h at h - h0; null: decoded
+  int32_t h0;
+  QDiv by;          // n_lo
+  const int2* str;  // strides of the upper spins, least significant first
+  int32_t n;        // upper spins
+  QDiv D;
+  __device__ inline int2 at(int32_t i) const {
+    int32_t h = by.div(i);
+    int2 off = lo[i - h * by.q];
+    if (hi) {
+      off.x += hi[h - h0].x;
+      off.y += hi[h - h0].y;
+    } else {
+      for (int32_t d = 0; d < n; ++d) {
+        const int32_t up = D.div(h);
+        off.x += (h - up * D.q) * str[d].x;
+        off.y += (h - up * D.q) * str[d].y;
+        h = up;
+      }
+    }
+    return off;
+  }
+};
+
+// Most entries of a split table's two parts (two tables fit LDS).
+constexpr int32_t kSplitLo = 2048, kSplitHi = 6144;
+
+// The table of indices [i0, i1) over n spins whose strides in A and B are
+// str[d], least significant spin d = 0, at `mem` (LDS, next free entry in
+// `used`).  The caller synchronises before the table is read.
+__device__ inline SplitTab split_tab(int2* mem, int32_t& used, int32_t tid, int32_t i0, int32_t i1,
+                                     const int2* str, int32_t n, const QDiv& D) {
+  int32_t r = 0, n_lo = 1;
+  while (r < n && n_lo * D.q <= kSplitLo && (r == 0 || n_lo < i1 - i0)) {
+    n_lo *= D.q;
+    ++r;
+  }
+  const QDiv by = qdiv_of(max(n_lo, 2));  // (n = 0: the index is 0)
+  const int32_t h0 = by.div(i0), n_hi = by.div(i1 - 1) - h0 + 1;
+  const bool both = n_hi <= kSplitHi;
+  int2* lo = mem + used;
+  int2* hi = lo + n_lo;
+  const int32_t all = n_lo + (both ? n_hi : 0);
+  used += all;
+  for (int32_t i = tid; i < all; i += kBlock) {
+    const bool low = i < n_lo;
+    int32_t x = low ? i : h0 + (i - n_lo);
+    const int32_t d1 = low ? r : n;
+    int2 off{0, 0};
+    for (int32_t d = low ? 0 : r; d < d1; ++d) {
+      const int32_t up = D.div(x);
+      const int32_t v = x - up * D.q;
+      off.x += v * str[d].x;
+      off.y += v * str[d].y;
+      x = up;
+    }
+    lo[i] = off;
+  }
+  return SplitTab{lo, both ? hi : nullptr, h0, by, str + r, n - r, D};
 }
 
 // STEP_TILES: `tile` consecutive outputs of C (row-major over b, m, n), over
-// contracted range ks of the split.  Tile tasks use none of the serial-task
-// LDS areas, so the whole dynamic LDS (tab_cap entries) holds generated offset
-// tables: contracted group first (only this task's segment of it when the
-// contracted index is split), then columns, rows, batch; the last entries
-// are kept for the partial sums of a one-output tile.
-//
-// A tile of one output over a long segment (the scalar product that ends a
-// knot's contraction, split over many tasks) is summed by all wavefronts, an
-// equal part of the segment each; thread 0 adds the partial sums in wavefront
-// order.
+// contracted range ks of the split.  Bound by the memory its operands come
+// from (a contracted index of 1 or 3, mostly), as long as enough loads are in
+// flight: offsets come from split tables in LDS, and
+//   - up to 64 contracted entries: lane k holds the offsets of entry k, a
+//     thread computes two outputs together and issues the loads of three
+//     entries of both before their products;
+//   - more of them: L lanes share an output, four entries each per round;
+//   - one output over a long segment (the scalar product that ends a knot's
+//     contraction, split over many tasks): all wavefronts, an equal part of
+//     the segment each; thread 0 adds the partial sums in wavefront order.
 //
 // ph (traced launches, thread 0; else null; ph[3] holds the task's start):
 // from the start to the end of the tables and operand states, then the
 // products, then the publish.
 template <class T>
 __device__ __attribute__((always_inline)) void tile_step(const DevProg& p, const StepDesc& s, int32_t tile_id, int32_t q,
-                          Cx<T>* arena, int32_t* s_tab, int32_t tab_cap, const States& st,
-                          T* s_red, int64_t* ph) {
+                          Cx<T>* arena, uint8_t* smem, const States& st, T* s_red, int64_t* ph) {
   const int32_t tid = task_tid();
-  GenIx ix = step_ix(p, s, q);
+  const int32_t lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  constexpr int32_t kWaves = kBlock / 64;
+  const QDiv D = qdiv_of(q);
+  const int32_t rb = s.ranks & 255, rm = (s.ranks >> 8) & 255, rk = (s.ranks >> 16) & 255,
+                rn = (s.ranks >> 24) & 255;
   const int64_t outs = (int64_t)s.nb * s.nm * s.nn;
   const int32_t base = s.n_tiles / s.n_ks;
   const int32_t ks = tile_id / base, t = tile_id - ks * base;
-  const int32_t k0 = ks * s.kseg, k1 = min(s.nk, k0 + s.kseg);
-  const int64_t o0 = (int64_t)t * s.tile;
-  const int64_t o1 = o0 + s.tile < outs ? o0 + s.tile : outs;
-  constexpr int32_t kWaves = kBlock / 64;
-  constexpr int32_t kPartials = 4 * kWaves;  // a complex partial sum (16 bytes) per wavefront
-  const int32_t n_of[6] = {s.nb, s.nm, k1 - k0, s.nb, k1 - k0, s.nn};
-  ix.klo = k0;
-  int32_t used = 0;
-  for (int g : {2, 4, 5, 1, 0, 3}) {
-    if (used + n_of[g] > tab_cap - 2 * kPartials) continue;
-    const int32_t lo = g == 2 || g == 4 ? k0 : 0;
-    int32_t* tb = s_tab + used;
-    for (int32_t i = tid; i < n_of[g]; i += kBlock)
-      tb[i] = group_off(lo + i, ix.str[g], ix.rank[g], ix.D);
-    ix.tab[g] = tb;
-    used += n_of[g];
+  const int32_t k0 = ks * s.kseg, k1 = min(s.nk, k0 + s.kseg), nk = k1 - k0;
+  const int32_t o0 = t * s.tile;
+  const int32_t o1 = (int32_t)min((int64_t)o0 + s.tile, outs);
+  // LDS: partial sums of the wavefronts, strides, tables
+  LdsCx<double>* part = (LdsCx<double>*)smem;
+  int2* dig = reinterpret_cast<int2*>(smem + kWaves * sizeof(Cx<double>));
+  const int32_t R = rb + rm + rn;
+  // strides in A and B of the output's spins n, m, b and of the contracted
+  // ones, least significant first (stored: A_b A_m A_k B_b B_k B_n, most first)
+  if (tid < R + rk) {
+    int32_t x = tid, ia = -1, ib = -1;
+    if (x < rn) {
+      ib = 2 * rb + rm + 2 * rk + rn - 1 - x;
+    } else if ((x -= rn) < rm) {
+      ia = rb + rm - 1 - x;
+    } else if ((x -= rm) < rb) {
+      ia = rb - 1 - x;
+      ib = rb + rm + rk + rb - 1 - x;
+    } else {
+      x -= rb;
+      ia = rb + rm + rk - 1 - x;
+      ib = 2 * rb + rm + 2 * rk - 1 - x;
+    }
+    const int32_t* sp = p.strides + s.str;
+    dig[tid] = int2{ia >= 0 ? sp[ia] : 0, ib >= 0 ? sp[ib] : 0};
   }
   int64_t ec;
   const T scale = step_scale<T>(st, s.a, s.b, ec);
+  __syncthreads();
+  int2* mem = dig + 64;
+  int32_t used = 0;
+  const SplitTab to = split_tab(mem, used, tid, o0, o1, dig, R, D);
+  const SplitTab tk_ = split_tab(mem, used, tid, k0, k1, dig + R, rk, D);
   __syncthreads();
   int64_t tk = 0;
   if (ph) {
@@ -910,42 +1185,114 @@ __device__ __attribute__((always_inline)) void tile_step(const DevProg& p, const
   Cx<T>* pc = s.n_ks > 1 ? arena + s.partial + (int64_t)ks * outs : arena + s.home_c;
   const GlbCx<T>* pa = (const GlbCx<T>*)(arena + s.home_a);
   const GlbCx<T>* pb = (const GlbCx<T>*)(arena + s.home_b);
+  const GlbOut<T> out((GlbCx<T>*)pc + o0);
+  const Cx<T> zero{0, 0};
   T lm = 0;
-  if (o1 - o0 == 1 && k1 - k0 >= 2 * kBlock) {
-    LdsCx<T>* part = (LdsCx<T>*)(s_tab + ((used + 3) & ~3));  // 16-byte aligned
-    const int32_t w = tid >> 6, lane = tid & 63;
-    const int32_t run = (k1 - k0 + kWaves - 1) / kWaves;
-    const int32_t kw0 = min(k1, k0 + w * run), kw1 = min(k1, kw0 + run);
-    const int32_t mn = s.nm * s.nn, o = (int32_t)o0;
-    const int32_t b = o / mn, m = (o - b * mn) / s.nn, n = o - b * mn - m * s.nn;
-    T cr, ci;
-    lane_dot<T>(pa + ix.a_row(b, m), pb + ix.b_col(b, n), ix, kw0 + lane, kw1, 64, cr, ci);
-    for (int32_t off = 32; off >= 1; off >>= 1) {
-      cr += __shfl_xor(cr, off, 64);
-      ci += __shfl_xor(ci, off, 64);
+  auto store = [&](int32_t o, Cx<T> c) {
+    c.re *= scale;
+    c.im *= scale;
+    put(out, o - o0, c);
+    lm = fmax(lm, fmax(fabs(c.re), fabs(c.im)));
+  };
+  // sum over the entries k_first, k_first + L, ... < k_end, four per round
+  auto dot = [&](int2 f, int32_t k, int32_t k_end, int32_t L) {
+    Cx<T> c = zero, c2 = zero;
+    for (; k < k_end; k += 4 * L) {
+      Cx<T> x[4], y[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        x[j] = y[j] = zero;
+        if (k + j * L < k_end) {
+          const int2 e = tk_.at(k + j * L);
+          x[j] = ldc(pa + (f.x + e.x));
+          y[j] = ldc(pb + (f.y + e.y));
+        }
+      }
+      cfma(c, x[0], y[0]);
+      cfma(c2, x[1], y[1]);
+      cfma(c, x[2], y[2]);
+      cfma(c2, x[3], y[3]);
     }
-    if (lane == 0) put(part, w, Cx<T>{cr, ci});
+    return Cx<T>{c.re + c2.re, c.im + c2.im};
+  };
+  const int32_t L = lanes_per_output(o1 - o0, nk);
+  if (o1 - o0 == 1 && nk >= 2 * kBlock) {
+    const int32_t run = (nk + kWaves - 1) / kWaves;
+    const int32_t kw0 = min(k1, k0 + wv * run), kw1 = min(k1, kw0 + run);
+    Cx<T> c = dot(to.at(o0), kw0 + lane, kw1, 64);
+    for (int32_t m = 32; m >= 1; m >>= 1) {
+      c.re += __shfl_xor(c.re, m, 64);
+      c.im += __shfl_xor(c.im, m, 64);
+    }
+    if (lane == 0) {
+      part[wv].re = c.re;
+      part[wv].im = c.im;
+    }
     __syncthreads();
     if (tid == 0) {
-      T re = 0, im = 0;
+      c = zero;
       for (int i = 0; i < kWaves; ++i) {
-        re += part[i].re;
-        im += part[i].im;
+        c.re += (T)part[i].re;
+        c.im += (T)part[i].im;
       }
-      re *= scale;
-      im *= scale;
-      put(GlbOut<T>((GlbCx<T>*)pc + o0), 0, Cx<T>{re, im});
-      lm = fmax(fabs(re), fabs(im));
+      store(o0, c);
+    }
+  } else if (L == 1 && nk <= 64) {
+    const int2 dk = lane < nk ? tk_.at(k0 + lane) : int2{0, 0};
+    for (int32_t o = o0 + tid; o < o1; o += 2 * kBlock) {
+      const int32_t o2 = o + kBlock;
+      const bool two = o2 < o1;
+      const int2 f = to.at(o), f2 = two ? to.at(o2) : f;
+      Cx<T> c = zero, c2 = zero;
+      int32_t k = 0;
+      for (; k + 3 <= nk; k += 3) {
+        Cx<T> x[3], y[3], x2[3], y2[3];
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+          const int32_t ka = rl(dk.x, k + j), kb = rl(dk.y, k + j);
+          x[j] = ldc(pa + (f.x + ka));
+          y[j] = ldc(pb + (f.y + kb));
+          x2[j] = y2[j] = zero;
+          if (two) {
+            x2[j] = ldc(pa + (f2.x + ka));
+            y2[j] = ldc(pb + (f2.y + kb));
+          }
+        }
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+          cfma(c, x[j], y[j]);
+          cfma(c2, x2[j], y2[j]);
+        }
+      }
+      for (; k < nk; ++k) {
+        const int32_t ka = rl(dk.x, k), kb = rl(dk.y, k);
+        const Cx<T> x = ldc(pa + (f.x + ka)), y = ldc(pb + (f.y + kb));
+        Cx<T> x2 = zero, y2 = zero;
+        if (two) {
+          x2 = ldc(pa + (f2.x + ka));
+          y2 = ldc(pb + (f2.y + kb));
+        }
+        cfma(c, x, y);
+        cfma(c2, x2, y2);
+      }
+      store(o, c);
+      if (two) store(o2, c2);
     }
   } else {
-    const int32_t L = lanes_per_output(o1 - o0, k1 - k0);
-    lm = step_outputs<T>(pa, pb, GlbOut<T>((GlbCx<T>*)pc + o0), ix, s.nm, s.nn, k0, k1, o0, o1,
-                         scale, L, tid, kBlock);
+    const int32_t lsub = tid & (L - 1);
+    for (int32_t o = o0 + tid / L; o < o1; o += kBlock / L) {
+      Cx<T> c = dot(to.at(o), k0 + lsub, k1, L);
+      for (int32_t m = L >> 1; m >= 1; m >>= 1) {
+        c.re += __shfl_xor(c.re, m, 64);
+        c.im += __shfl_xor(c.im, m, 64);
+      }
+      if (lsub == 0) store(o, c);
+    }
   }
   if (ph) {
-    const int64_t t = wall_clock64();
-    ph[1] = t - tk;
-    tk = t;
+    const int64_t t2 = wall_clock64();
+    ph[1] = t2 - tk;
+    tk = t2;
   }
   if (s.n_ks == 1) tile_publish<T>(p, s.c, tile_id, lm, ec, s_red);
   if (ph) ph[2] = wall_clock64() - tk;
@@ -1240,7 +1587,7 @@ __device__ __attribute__((always_inline)) void gemm_tile(const DevProg& p, const
                (const GlbCx<T>*)(arena + s.home_b),
                (GlbCx<T>*)(s.n_ks > 1 ? arena + s.partial + (int64_t)ks * outs : arena + s.home_c),
                str, kl <= kcap ? ktab : nullptr, rb, rm, rk, rn, s.nm, s.nn, k0, kl, scale, smem,
-               QDiv(q)};
+               qdiv_of(q)};
   __syncthreads();
   if (g.ktab) {
     for (int32_t i = tid; i < kl; i += kBlock) {
@@ -1310,10 +1657,18 @@ __device__ __attribute__((always_inline)) void reduce_step(const DevProg& p, con
   T lm = 0;
   for (int64_t o = o0 + threadIdx.x; o < o1; o += kBlock) {
     T cr = 0, ci = 0;
-    for (int32_t j = 0; j < s.n_ks; ++j) {
-      const Cx<T> v = ldc(P + (int64_t)j * outs + o);
-      cr += v.re;
-      ci += v.im;
+    for (int32_t j = 0; j < s.n_ks; j += 8) {
+      Cx<T> v[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        v[i] = Cx<T>{0, 0};
+        if (j + i < s.n_ks) v[i] = ldc(P + (int64_t)(j + i) * outs + o);
+      }
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        cr += v[i].re;
+        ci += v[i].im;
+      }
     }
     put(C, (int32_t)(o - o0), Cx<T>{cr, ci});
     lm = fmax(lm, fmax(fabs(cr), fabs(ci)));
@@ -1339,7 +1694,8 @@ __device__ __attribute__((always_inline)) void knot_final(const DevProg& p, cons
     const Cx<T> r = *tptr<T>(p.tens[t], arena, lds);
     int32_t sh;
     int64_t et;
-    st.get(t, sh, et);
+    if (st.local(t)) st.get(t, sh, et);
+    else st.get_late(t, sh, et);
     e += et;
     acc_mul(z, e, Cx<double>{(double)r.re, (double)r.im});
   }
@@ -1388,7 +1744,8 @@ __device__ inline Cx<double> cdiv(Cx<double> a, Cx<double> b) {
 // x_m / (x_m + q - 1), a loop factor x_e gives 1, and each original edge takes
 // the value of its merged edge (x_m is the product of its members' e^{J}).
 // One wavefront per vertex tensor; the whole workgroup calls this, after the
-// persistent kernel (tensor states and data are then all in global memory).
+// persistent kernel (what it reads, the adjoints and their components' scalars
+// with their states, is then in global memory).
 template <class T>
 __device__ void knot_gradient(const DevProg& p, const KnotDesc& kd, const Cx<T>* arena,
                               double* grad) {
@@ -1408,7 +1765,7 @@ __device__ void knot_gradient(const DevProg& p, const KnotDesc& kd, const Cx<T>*
     for (int j = 0; j < kMaxSlots; ++j) x[j] = j < ns ? xm[slot_me[j]] : Cx<double>{1.0, 0.0};
     int32_t qn = 1;
     for (int j = 0; j < ns; ++j) qn *= q;
-    // gradient plans keep every tensor and state in global memory
+    // (adjoints of vertex tensors live in global memory)
     const TensorDesc td = p.tens[vd.adjoint];
     const Cx<T>* fb = arena + td.off;
     double ar[kMaxSlots], ai[kMaxSlots];
@@ -1682,14 +2039,12 @@ __global__ __launch_bounds__(kBlock, 2) void engine(const uint8_t* __restrict__ 
                                                  TraceRec* __restrict__ trace) {
   __shared__ int32_t s_task;
   __shared__ T s_red[kBlock / 64];
-  __shared__ int32_t s_tb[kDescBuf + 1];
   __shared__ int64_t s_ph[4];
   __shared__ int32_t s_chk[2];
   int32_t* s_tab = reinterpret_cast<int32_t*>(kn_dyn_smem + kLdsTab);
-  StepDesc* s_desc = reinterpret_cast<StepDesc*>(kn_dyn_smem + kLdsDesc);
   int32_t* s_shift = reinterpret_cast<int32_t*>(kn_dyn_smem + kLdsShift);
   int64_t* s_exp = reinterpret_cast<int64_t*>(kn_dyn_smem + kLdsExp);
-  TensorState* s_ext = reinterpret_cast<TensorState*>(kn_dyn_smem + kLdsExt);
+  FlatRec* s_rec = reinterpret_cast<FlatRec*>(kn_dyn_smem + kLdsRec);
   Cx<T>* lds = reinterpret_cast<Cx<T>*>(kn_dyn_smem + kLdsArena);
   const DevProg p = make_prog(img, state);
   const int32_t n_queue = p.h->n_queue;
@@ -1746,15 +2101,20 @@ __global__ __launch_bounds__(kBlock, 2) void engine(const uint8_t* __restrict__ 
       const KnotDesc kd = p.knots[td.knot];
       const int32_t slice = p.uslice[td.knot];
       const States st{p.ts, s_shift, s_exp, td.state_lo, min(td.state_len, kStateCap)};
+      // an output's shift is the maximum over its step's units
+      for (int32_t i = tid; i < st.len; i += kBlock) s_shift[i] = kShiftNone;
+      __syncthreads();
       int64_t ph_buf[4] = {0, 0, 0, 0};
       int64_t* ph = (trace && tid == 0) ? ph_buf : nullptr;
       if (td.flags & TF_SETUP) {
-        knot_setup<T>(p, kd, arena, lds, J, st, slice);
+        // (the staging area is free while the vertex tensors are built)
+        knot_setup<T>(p, kd, arena, lds, (LdsCx<double>*)(kn_dyn_smem + kLdsArena + p.h->lds_bytes),
+                      stage_bytes(p.h->lds_bytes) / (int32_t)sizeof(Cx<double>), J, st, slice);
         __syncthreads();
       }
       if (ph) ph[0] = wall_clock64() - t_start;
-      serial_steps<T>(p, td.first, td.count, kd.q, arena, lds, s_tab, s_desc, s_tb, s_ext, st,
-                      s_red, ph);
+      serial_steps<T>(p, td.first, td.count, kd.q, arena, lds, reinterpret_cast<int2*>(s_tab),
+                      s_rec, st, td.state_len, ph);
       if (td.flags & TF_FINAL) knot_final<T>(p, kd, arena, lds, zout, st, slice);
       if (ph)
         for (int i = 0; i < 4; ++i) s_ph[i] = ph[i];
@@ -1795,7 +2155,7 @@ __global__ __launch_bounds__(kBlock, 2) void engine(const uint8_t* __restrict__ 
       else if (sd.mode == STEP_GEMM64)
         gemm_tile<T, true>(p, sd, td.count, q, arena, kn_dyn_smem, dyn, st, s_red, ph);
       else
-        tile_step<T>(p, sd, td.count, q, arena, s_tab, dyn / 4, st, s_red, ph);
+        tile_step<T>(p, sd, td.count, q, arena, kn_dyn_smem, st, s_red, ph);
       if (ph) ph[3] = 0;
     }
     // ---- publish; the last task of a group releases the knot's next group.

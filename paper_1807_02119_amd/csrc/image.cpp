@@ -320,17 +320,26 @@ void make_section(PlanKnot& k) {
     pg.swap(out);
   }
 
-  // ---- LDS homes: tensors produced and consumed inside one serial group
-  // (gradient plans read every tensor again in the reverse pass: all global)
-  if (!k.gradient) {
+  // ---- LDS homes: tensors produced and last read inside one serial group.  In
+  // a gradient plan forward tensors are read again by the reverse steps, and
+  // the component scalars and the adjoints of the vertex tensors are read after
+  // the launch: those are global.
+  {
     const int32_t nt = (int32_t)k.tensors.size();
     const int32_t ns = (int32_t)k.steps.size();
-    std::vector<int32_t> consumer(nt, -1);  // step index, or ns for the final product
+    // last reader: step index, or ns for the final product
+    std::vector<int32_t> consumer(nt, -1);
+    std::vector<uint8_t> global(nt, 0);
     for (int32_t si = 0; si < ns; ++si) {
       consumer[k.steps[si].a] = si;
       consumer[k.steps[si].b] = si;
     }
     for (int32_t c : k.comps) consumer[c] = ns;
+    if (k.gradient) {
+      for (int32_t c : k.comps) global[c] = 1;
+      for (const auto& v : k.vtx)
+        if (v.adjoint >= 0) global[v.adjoint] = 1;
+    }
     const int64_t es = elem_bytes(k.precision);
     const int64_t cap = k.lds_bytes / es;
     // each task of a forked group runs on its own workgroup: one LDS arena
@@ -348,7 +357,7 @@ void make_section(PlanKnot& k) {
       const int32_t lo = range.first, hi = range.first + range.second;  // steps [lo, hi)
       auto inside = [&](int32_t t) {
         int32_t c = consumer[t];
-        if (c < 0) return false;
+        if (c < 0 || global[t]) return false;
         if (c == ns) return (g.flags & TF_FINAL) != 0;
         return c >= lo && c < hi;
       };
@@ -379,7 +388,7 @@ void make_section(PlanKnot& k) {
         for (int32_t u = si; u < sj; ++u) {
           const PStep& s = k.steps[u];
           for (int32_t op : {s.a, s.b})
-            if (S.td[op].lds_off >= 0) la.release(S.td[op].lds_off, k.tensors[op].size);
+            if (S.td[op].lds_off >= 0 && consumer[op] == u) la.release(S.td[op].lds_off, k.tensors[op].size);
         }
         si = sj;
       }

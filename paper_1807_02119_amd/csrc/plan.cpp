@@ -1299,8 +1299,10 @@ kn_status lay_out(PlanKnot& k, const kn_plan_opts& o, kn_plan_stats& st, int32_t
     };
     const kn_bucket_opts& bo = o.bucket[bk];
     bool big = macs >= std::ldexp(1.0, k.big_log2) || outs >= std::ldexp(1.0, k.big_outs_log2);
-    // a serial step generates its gather tables in LDS; larger ones are tiled
-    if (2 * nb + nm + 2 * nk + nn > kTabBuf) big = true;
+    // a serial step's spin groups have at most kTabBuf entries together, and
+    // its offsets are formed from strides below 2^24; larger ones are tiled
+    if (2 * nb + nm + 2 * nk + nn > kTabBuf || std::max(nb * nm * nk, nb * nk * nn) > 16777216.0)
+      big = true;
     if (!big) continue;
     PTiling& t = k.tiling[i];
     double base;
@@ -1473,7 +1475,7 @@ kn_status make_plan(const kn_tait& g, int32_t q, const kn_plan_opts& o, PlanKnot
   // a step's outputs from one base (at most 2^24 of them)
   k.big_log2 = std::min(o.big_step_macs_log2 > 0 ? o.big_step_macs_log2 : 16, 24);
   k.big_outs_log2 = std::min(o.big_step_outs_log2 > 0 ? o.big_step_outs_log2 : kBigOutsLog2, 24);
-  k.lds_bytes = o.lds_bytes > 0 ? o.lds_bytes : 24576;
+  k.lds_bytes = o.lds_bytes > 0 ? o.lds_bytes : kLdsDefault;
   k.split_est = std::ldexp(1.0, o.split_serial_log2 > 0 ? o.split_serial_log2 : kSplitSerialLog2);
   k.fork_est = std::ldexp(1.0, o.fork_serial_log2 > 0 ? o.fork_serial_log2 : kForkSerialLog2);
   {

@@ -25,8 +25,9 @@ constexpr int32_t kMagic = 0x4b4e4732;  // "KNG2"
 // engine's registers allow.
 constexpr int32_t kBlock = 512;
 // Fixed LDS areas of a workgroup (the tensor arena follows them):
-constexpr int32_t kTabBuf = 3072;   // gather-table entries generated per chunk of serial steps
-constexpr int32_t kDescBuf = 64;    // step descriptors staged per chunk
+constexpr int32_t kTabBuf = 3072;   // words of the digit strides of a chunk of serial steps (and the
+                                    // most entries a serial step's spin groups may have together)
+constexpr int32_t kDescBuf = 64;    // steps per chunk
 constexpr int32_t kStateCap = 768;  // tensor states cached for the running serial task
 
 enum TaskKind : int32_t {
@@ -217,8 +218,8 @@ struct TraceRec {
   int64_t t_end;    // execution finished
   int32_t task;
   int32_t wg;
-  // serial tasks: time in setup, in staging descriptors and generating
-  // tables, in the step products, in reductions and barriers; tile tasks:
+  // serial tasks: time in setup, in staging descriptors and digit strides,
+  // in the step products, in the barriers after each level; tile tasks:
   // from the start to the end of tables and operand states (descriptor loads
   // included), the products, the publish of C's shift (0 for reduce tasks)
   int64_t ph[4];
@@ -228,11 +229,18 @@ constexpr int32_t kShiftNone = (-2147483647 - 1);
 
 // Byte offsets of the LDS areas; the tensor arena starts at kLdsArena.
 constexpr int32_t kLdsTab = 0;
-constexpr int32_t kLdsDesc = kLdsTab + kTabBuf * 4;
-constexpr int32_t kLdsShift = kLdsDesc + kDescBuf * (int32_t)sizeof(StepDesc);
-constexpr int32_t kLdsExp = (kLdsShift + kStateCap * 4 + 7) / 8 * 8;
-constexpr int32_t kLdsExt = (kLdsExp + kStateCap * 8 + 15) / 16 * 16;  // operand states
-constexpr int32_t kLdsArena = kLdsExt + 2 * kDescBuf * (int32_t)sizeof(TensorState);
+constexpr int32_t kLdsShift = kLdsTab + kTabBuf * 4;
+// states: those of the tensors a serial task makes, then those of a chunk's
+// operands made before the task
+constexpr int32_t kStates = kStateCap + 2 * kDescBuf;
+constexpr int32_t kLdsExp = (kLdsShift + kStates * 4 + 7) / 8 * 8;
+constexpr int32_t kFlatRecBytes = 64;  // a step's record for the lanes that compute it
+constexpr int32_t kLdsRec = (kLdsExp + kStates * 8 + 15) / 16 * 16;
+constexpr int32_t kLdsArena = kLdsRec + kDescBuf * kFlatRecBytes;
+// Default LDS arena of a plan (kn_plan_opts.lds_bytes).  One workgroup fills a
+// compute unit whatever it is; an arena of 24 KiB left two thirds of a
+// 600-crossing knot's operands in global memory (launch 312 us; 298 with 96 KiB).
+constexpr int32_t kLdsDefault = 96 * 1024;
 // Dynamic LDS the engine may use, and the staging area after the tensor arena
 // (lds_bytes of it): global operands of a serial step that the whole
 // workgroup computes are copied there when they fit, so that the step's

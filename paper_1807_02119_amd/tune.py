@@ -7,7 +7,7 @@ How a step runs is decided by planner knobs:
 - tile_macs_log2 / tile_outs_log2: how much work, and at most how many
   outputs, one tile of outputs carries;
 - lds_bytes: the per-workgroup LDS arena for tensors that stay inside one
-  serial task, which also sets how many workgroups fit on a compute unit;
+  serial task;
 - gemm_tasks_log2: how many tasks a step computed in output blocks is cut
   into (several blocks per task above that);
 - gemm64_pct: how much padding a step accepts to use 64 x 64 output blocks
@@ -49,7 +49,7 @@ SPACE = {
     "big_step_outs_log2": [10, 11, 12, 13, 14, 31],
     "tile_macs_log2": [13, 14, 15, 16, 17],
     "tile_outs_log2": [8, 9, 10, 11, 12, 14],
-    "lds_bytes": [16384, 24576, 32768, 49152],
+    "lds_bytes": [16384, 24576, 32768, 49152, 98304],
     "gemm_tasks_log2": [4, 5, 6, 7, 30],
     "gemm64_pct": [1, 150, 300],
     "split_serial_log2": [8, 10, 12, 40],
@@ -64,7 +64,7 @@ BUCKET_SPACE = {
 }
 N_BUCKETS = 5
 DEFAULTS = {"big_step_macs_log2": 16, "big_step_outs_log2": 12, "tile_macs_log2": 15,
-            "tile_outs_log2": 10, "lds_bytes": 24576, "gemm_tasks_log2": 5, "gemm64_pct": 300,
+            "tile_outs_log2": 10, "lds_bytes": 98304, "gemm_tasks_log2": 5, "gemm64_pct": 300,
             "split_serial_log2": 40, "split_min_log2": 12, "fork_serial_log2": 10, "grid": 0}
 DEFAULTS_KEY = json.dumps(DEFAULTS, sort_keys=True)
 TUNED_DIR = os.path.join(os.path.dirname(os.path.abspath(__file__)), "tuned")
