@@ -157,7 +157,7 @@ __device__ inline auto ldc(P p) {
   return Cx<T>{p->re, p->im};
 }
 
-// Output entries.  Tensor entries in global memory are written through the
+// Output entries.  Tile tasks write tensor entries in global memory through the
 // L2 to memory (system-scope cache policy, sc0 sc1) instead of leaving dirty
 // lines there: a task that finishes then has little left to write back when
 // it releases its results at device scope (the release itself is
@@ -193,21 +193,19 @@ __device__ inline void put(const GlbOut<float>& o, int32_t i, Cx<float> v) {
   const F2 x = {v.re, v.im};
   __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(U2, x), o.r, i * 8, 0, kWriteThrough);
 }
+// Serial tasks store plainly: most of what they write is read again by the
+// same workgroup, and scattered entries written through cost the task more
+// than the release then does (117-knot batch 930 -> 820 us, mixed-q values 1187
+// -> 1040 us).
+template <class T>
+__device__ inline void put(GlbCx<T>* p, int32_t i, Cx<T> v) {
+  p[i].re = v.re;
+  p[i].im = v.im;
+}
 template <class T>
 __device__ inline void put(LdsCx<T>* p, int32_t i, Cx<T> v) {
   p[i].re = v.re;
   p[i].im = v.im;
-}
-
-// One entry written through the L2 by a lane on its own (where the lanes of a
-// wavefront write to different tensors, which no one buffer resource covers).
-__device__ inline void put_through(Cx<double>* p, Cx<double> v) {
-  __hip_atomic_store(&p->re, v.re, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-  __hip_atomic_store(&p->im, v.im, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-}
-__device__ inline void put_through(Cx<float>* p, Cx<float> v) {
-  __hip_atomic_store(reinterpret_cast<uint64_t*>(p), __builtin_bit_cast(uint64_t, v), __ATOMIC_RELAXED,
-                     __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // Tensor states: those produced by the running serial task are cached in LDS,
@@ -460,7 +458,7 @@ __device__ __attribute__((always_inline)) void knot_setup(const DevProg& p, cons
       if (x0 + lane < total) {
         const Cx<T> v{(T)acc.re, (T)acc.im};
         if (lds_off >= 0) put((LdsCx<T>*)(lds + lds_off), i, v);
-        else put_through(arena + (int64_t)(((uint64_t)(uint32_t)off_hi << 32) | (uint32_t)off_lo) + i, v);
+        else put((GlbCx<T>*)(arena + (int64_t)(((uint64_t)(uint32_t)off_hi << 32) | (uint32_t)off_lo)), i, v);
       }
     }
   }
@@ -510,14 +508,17 @@ __device__ inline T step_scale(const States& st, int32_t a, int32_t b, int64_t& 
 //     wavefronts 64 at a time, each lane with the step of its output: a level
 //     of 64 steps of 9 to 27 outputs takes each wavefront three rounds, not
 //     the eight steps one after another that it took a wavefront per step;
+//   - a lane computes a tile of up to 3 x 3 outputs that share rows and columns,
+//     where a level has more outputs than the workgroup has lanes;
 //   - only a level ends with a barrier: an output's shift is the maximum over
 //     its entries, kept by an LDS atomic.
-// Steps with a long contracted index (more than two spins) run as units: 2^l
+// Steps with a long contracted index (more than two spins, or three where the
+// outputs are many) run as units: 2^l
 // lanes share an output, and units of up to about kUnitMacs multiply-adds are
 // taken by the wavefronts in turn.
-// Figures: the launch of one 600-crossing knot (q = 3, complex128) 480 -> 218 us,
-// of one 250-crossing knot with q = 5 170 -> 108 us, of gradients of 8 knots
-// 700 -> 300 us, all with the LDS arena of 96 KiB.
+// Figures: the launch of one 600-crossing knot (q = 3, complex128) 480 -> 200 us,
+// of one 250-crossing knot with q = 5 170 -> 105 us; a 263-step run of the
+// 117-knot batch 440 -> 250 us (LDS arena of 96 KiB but for the last).
 constexpr int32_t kUnitMacs = 1024;
 constexpr float kStageMacs = 4096.0f;
 constexpr int32_t kDigCap = kTabBuf / 2;  // digit strides (pairs) of a chunk
@@ -526,10 +527,11 @@ static_assert(kDescBuf == 64, "lane j holds step j of a chunk");
 // A flat step as its lanes read it from LDS.
 struct alignas(16) FlatRec {
   int32_t o_start;     // its first output among those of the chunk's flat steps
-  int32_t i_start;     // its first item (q outputs) among theirs
+  int32_t i_start;     // its first item among theirs
   int32_t dig_off;     // its digit strides
-  int32_t R, o_step;   // output digits; outputs per value of the highest one
-  int32_t q0, q1;      // values of the lowest contracted digit and of the one above (1: none)
+  int32_t ranks;       // as in StepDesc
+  int32_t nn, nm;      // columns and rows
+  int32_t sn, sm;      // columns (rows) per value of the highest column (row) digit
   int32_t ha, hb, hc;  // homes
   int32_t ia, ib, ic;  // states of A, B and C in the state arrays
 };
@@ -684,7 +686,7 @@ __device__ __attribute__((always_inline)) uint32_t unit_round(const UnitCtx<T>& 
     if (lsub == 0 && oi < u.o1) {
       c[i].re *= u.scale;
       c[i].im *= u.scale;
-      if (u.hc >= 0) put(GlbOut<T>((GlbCx<T>*)(arena + u.hc) + u.o0), oi - u.o0, c[i]);
+      if (u.hc >= 0) put((GlbCx<T>*)(arena + u.hc), oi, c[i]);
       else put((LdsCx<T>*)(lds + (-1 - u.hc)), oi, c[i]);
       top = max(top, max(mag_word(c[i].re), mag_word(c[i].im)));
     }
@@ -692,75 +694,113 @@ __device__ __attribute__((always_inline)) uint32_t unit_round(const UnitCtx<T>& 
   return top;
 }
 
-// One item of a flat step: outputs o + t q^(R - 1) for t < T, in step `r` of
-// the lane.  F says where the operands of all the lanes are: 0 LDS, 1 the global
-// arena, 2 either (generic loads, which wait for earlier stores too).
-template <int F, class T>
-__device__ inline void flat_item(const FlatRec& r, const int2* s_dig, int32_t o, int32_t n_t, uint32_t q,
-                                 uint32_t m18, Cx<T>* arena, Cx<T>* lds, const States& st, bool write) {
+// x / d for 0 <= x < 2^15 and d >= 1, from r = 1.0f / d: x + 0.5 is 0.5 / d or
+// more away from a multiple of d, and the product is off by less than 2^-7 / d.
+__device__ inline int32_t small_div(int32_t x, float r) { return (int32_t)(((float)x + 0.5f) * r); }
+
+// Rows (columns) of the tiles of a level's items, for steps of digits < q.
+__device__ inline int32_t flat_tile(int32_t q) { return q == 2 || q == 4 ? 2 : 3; }
+
+// One item of a flat step, `r` of the lane: a tile of outputs of one batch
+// entry, in up to NT rows (columns) that differ in the highest row (column)
+// digit alone; NT = 1: one output.  F says where the operands of all the lanes
+// are: 0 LDS, 1 the global arena, 2 either (generic loads, which wait for
+// earlier stores too).
+//
+// A lane's gathered entries are what bounds a level of many outputs (a load of
+// 64 scattered entries occupies the memory pipeline for some 40 clocks, at 16
+// for its products): a row's entry is multiplied with NT columns' and a
+// column's with NT rows'.
+template <int F, int NT, class T>
+__device__ inline void flat_item(const FlatRec& r, const int2* s_dig, int32_t x, int32_t q, uint32_t m18,
+                                 Cx<T>* arena, Cx<T>* lds, const States& st, bool write) {
   const int2* dg = s_dig + r.dig_off;
+  const int32_t rb = r.ranks & 255, rm = (r.ranks >> 8) & 255, rk = (r.ranks >> 16) & 255,
+                rn = (r.ranks >> 24) & 255;
+  const int32_t R = rb + rm + rn;
+  int32_t o = x, i0 = 0, j0 = 0, ni = 1, nj = 1;
+  if (NT > 1) {
+    // the tile's first row and column in the highest digits, and its output
+    // where these are zero
+    const int32_t bn = rn > 0 ? (q + NT - 1) / NT : 1, bm = rm > 0 ? (q + NT - 1) / NT : 1;
+    const int32_t y = small_div(x, 1.0f / (float)bn), z = small_div(y, 1.0f / (float)bm);
+    const int32_t u = small_div(z, 1.0f / (float)r.sn), b = small_div(u, 1.0f / (float)r.sm);
+    o = (b * r.nm + (u - b * r.sm)) * r.nn + (z - u * r.sn);
+    j0 = (x - y * bn) * NT;
+    i0 = (y - z * bm) * NT;
+    ni = rm > 0 ? min(NT, q - i0) : 1;
+    nj = rn > 0 ? min(NT, q - j0) : 1;
+  }
   int32_t fa = 0, fb = 0;
-  uint32_t x = (uint32_t)o;
+  uint32_t y = (uint32_t)o;
   // (the digits past the last are zero)
-  for (int32_t d = 0; __any(d < r.R); d += 4) {
+  for (int32_t d = 0; __any(d < R); d += 4) {
     int2 s4[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) s4[i] = dg[min(d + i, r.R)];
+    for (int i = 0; i < 4; ++i) s4[i] = dg[min(d + i, R)];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const uint32_t up = __umul24(x, m18) >> 18;
-      const uint32_t v = x - __umul24(up, q);
+      const uint32_t up = __umul24(y, m18) >> 18;
+      const uint32_t v = y - __umul24(up, (uint32_t)q);
       fa += (int32_t)__umul24(v, (uint32_t)s4[i].x);
       fb += (int32_t)__umul24(v, (uint32_t)s4[i].y);
-      x = up;
+      y = up;
     }
   }
-  // strides of the contracted digits (past them: other steps', not used) and
-  // of the highest output digit
-  const int2 s0 = dg[r.R], s1 = dg[r.R + 1], top = dg[max(r.R - 1, 0)];
-  const int32_t o_step = r.o_step;
-  const int32_t sh = shift_of(st.sh[r.ia]) + shift_of(st.sh[r.ib]);
-  const T scale = (T)ldexp(1.0, -sh);
+  // strides of the contracted digits and of the highest row and column digits
+  // (where there is none: other steps', not used)
+  const int2 s0 = dg[R], s1 = dg[R + 1], s2 = dg[R + 2];
+  const int32_t row = dg[max(rn + rm - 1, 0)].x, col = dg[max(rn - 1, 0)].y;
+  const int32_t q0 = rk > 0 ? q : 1, q1 = rk > 1 ? q : 1, q2 = rk > 2 ? q : 1;
+  if (NT > 1) {
+    fa += i0 * row;
+    fb += j0 * col;
+    o += i0 * r.sm * r.nn + j0 * r.sn;
+  }
   uint32_t mag = 0;
+  Cx<T> c[NT][NT];
+#pragma unroll
+  for (int i = 0; i < NT; ++i)
+#pragma unroll
+    for (int j = 0; j < NT; ++j) c[i][j] = Cx<T>{0, 0};
   auto run = [&](auto pa, auto pb) {
-    for (int32_t t = 0; t < n_t; t += 3) {
-      Cx<T> c[3] = {{0, 0}, {0, 0}, {0, 0}};
+    auto macs = [&](auto nk_, auto pa1, auto pb1) {
+      constexpr int NK = decltype(nk_)::value;
+      Cx<T> va[NK][NT], vb[NK][NT];
+#pragma unroll
+      for (int k = 0; k < NK; ++k)
+#pragma unroll
+        for (int i = 0; i < NT; ++i) {
+          va[k][i] = vb[k][i] = Cx<T>{0, 0};
+          if (i == 0 || i < ni) va[k][i] = ldc(pa1 + (k * s0.x + i * row));
+          if (i == 0 || i < nj) vb[k][i] = ldc(pb1 + (k * s0.y + i * col));
+        }
+#pragma unroll
+      for (int k = 0; k < NK; ++k)
+#pragma unroll
+        for (int i = 0; i < NT; ++i)
+#pragma unroll
+          for (int j = 0; j < NT; ++j) cfma(c[i][j], va[k][i], vb[k][j]);
+    };
+    // (two contracted entries at a time where three would take more registers
+    // than there are)
+    constexpr int NKT = NT == 3 ? 2 : 3;
+#pragma unroll 1
+    for (int32_t k2 = 0; k2 < q2; ++k2) {
       auto pa1 = pa;
       auto pb1 = pb;
-      for (int32_t k1 = 0; k1 < r.q1; ++k1) {
-        for (int32_t k0 = 0; k0 < r.q0; k0 += 3) {
-          Cx<T> va[3][3], vb[3][3];
-#pragma unroll
-          for (int k = 0; k < 3; ++k)
-#pragma unroll
-            for (int j = 0; j < 3; ++j) {
-              va[k][j] = vb[k][j] = Cx<T>{0, 0};
-              if (t + j < n_t && k0 + k < r.q0) {
-                va[k][j] = ldc(pa1 + ((k0 + k) * s0.x + j * top.x));
-                vb[k][j] = ldc(pb1 + ((k0 + k) * s0.y + j * top.y));
-              }
-            }
-#pragma unroll
-          for (int k = 0; k < 3; ++k)
-#pragma unroll
-            for (int j = 0; j < 3; ++j) cfma(c[j], va[k][j], vb[k][j]);
-        }
+#pragma unroll 1
+      for (int32_t k1 = 0; k1 < q1; ++k1) {
+        int32_t k0 = 0;
+#pragma unroll 1
+        for (; k0 + NKT <= q0; k0 += NKT) macs(std::integral_constant<int, NKT>{}, pa1 + k0 * s0.x, pb1 + k0 * s0.y);
+#pragma unroll 1
+        for (; k0 < q0; ++k0) macs(std::integral_constant<int, 1>{}, pa1 + k0 * s0.x, pb1 + k0 * s0.y);
         pa1 += s1.x;
         pb1 += s1.y;
       }
-      pa += 3 * top.x;
-      pb += 3 * top.y;
-#pragma unroll
-      for (int j = 0; j < 3; ++j) {
-        if (write && t + j < n_t) {
-          c[j].re *= scale;
-          c[j].im *= scale;
-          const int32_t oj = o + (t + j) * o_step;
-          if (r.hc < 0) put((LdsCx<T>*)(lds + (-1 - r.hc)), oj, c[j]);
-          else put_through(arena + r.hc + oj, c[j]);
-          mag = max(mag, max(mag_word(c[j].re), mag_word(c[j].im)));
-        }
-      }
+      pa += s2.x;
+      pb += s2.y;
     }
   };
   if constexpr (F == 0)
@@ -771,6 +811,21 @@ __device__ inline void flat_item(const FlatRec& r, const int2* s_dig, int32_t o,
     run((const Cx<T>*)(r.ha < 0 ? lds + (-1 - r.ha) : arena + r.ha) + fa,
         (const Cx<T>*)(r.hb < 0 ? lds + (-1 - r.hb) : arena + r.hb) + fb);
   if (write) {
+    const int32_t sh = shift_of(st.sh[r.ia]) + shift_of(st.sh[r.ib]);
+    const T scale = (T)ldexp(1.0, -sh);
+#pragma unroll
+    for (int i = 0; i < NT; ++i)
+#pragma unroll
+      for (int j = 0; j < NT; ++j) {
+        if (i < ni && j < nj) {
+          c[i][j].re *= scale;
+          c[i][j].im *= scale;
+          const int32_t oj = o + i * r.sm * r.nn + j * r.sn;
+          if (r.hc < 0) put((LdsCx<T>*)(lds + (-1 - r.hc)), oj, c[i][j]);
+          else put((GlbCx<T>*)(arena + r.hc), oj, c[i][j]);
+          mag = max(mag, max(mag_word(c[i][j].re), mag_word(c[i][j].im)));
+        }
+      }
     __hip_atomic_fetch_max((__attribute__((address_space(3))) int32_t*)&st.sh[r.ic], mag_shift<T>(mag),
                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     if (o == 0) st.ex[r.ic] = st.ex[r.ia] + st.ex[r.ib] + sh;
@@ -804,6 +859,7 @@ __device__ __attribute__((always_inline)) void serial_steps(const DevProg& p, in
   const int32_t stage_elems = stage_bytes(p.h->lds_bytes) / (int32_t)sizeof(Cx<T>);
   const int32_t end = first + count;
   const uint32_t m18 = small_magic(q);
+  const int32_t nt = flat_tile(q), q_tiles = (q + nt - 1) / nt;
   int32_t ce = 0;
   StepDesc next{};
   if (first + lane < end) next = p.steps[first + lane];
@@ -831,21 +887,25 @@ __device__ __attribute__((always_inline)) void serial_steps(const DevProg& p, in
            ((int64_t)outs << log_l) < (d.nk >> log_l >= 16 ? kBlock : 64))
       ++log_l;
     const int32_t pack = R | rk << 8 | log_l << 16 | (outs <= kSmallIndex && nkq <= kSmallIndex ? 1 << 24 : 0);
-    // flat: at most two contracted spins, and every state in LDS
+    // flat: at most two contracted spins, or three where the outputs fill the
+    // workgroup (few outputs of a long contracted index are better shared by
+    // several lanes each), and every state in LDS
     auto made_here = [&](int32_t t) { return (uint32_t)(t - st.lo) < (uint32_t)made; };
     auto in_lds = [&](int32_t t) { return st.local(t) || !made_here(t); };
-    const bool flat = lane < ce && rk <= 2 && outs <= kSmallIndex && in_lds(d.a) && in_lds(d.b) && st.local(d.c);
-    const int32_t o_step = R > 0 ? D.div(outs) : 1;
-    const int32_t f_end = wave_scan(flat ? outs : 0), i_end = wave_scan(flat ? o_step : 0);
+    const bool flat = lane < ce && (rk <= 2 || (rk == 3 && outs >= kBlock)) && outs <= kSmallIndex && in_lds(d.a) && in_lds(d.b) && st.local(d.c);
+    const int32_t sn = rn > 0 ? D.div(d.nn) : 1, sm = rm > 0 ? D.div(d.nm) : 1;
+    const int32_t items = d.nb * sn * sm * (rn > 0 ? q_tiles : 1) * (rm > 0 ? q_tiles : 1);
+    const int32_t f_end = wave_scan(flat ? outs : 0), i_end = wave_scan(flat ? items : 0);
     if (wv == 0 && flat) {
       FlatRec r;
       r.o_start = f_end - outs;
-      r.i_start = i_end - o_step;
-      r.o_step = o_step;
+      r.i_start = i_end - items;
       r.dig_off = dig_off;
-      r.R = R;
-      r.q0 = rk > 0 ? q : 1;
-      r.q1 = rk > 1 ? q : 1;
+      r.ranks = d.ranks;
+      r.nn = d.nn;
+      r.nm = d.nm;
+      r.sn = sn;
+      r.sm = sm;
       r.ha = d.home_a;
       r.hb = d.home_b;
       r.hc = d.home_c;
@@ -941,9 +1001,8 @@ __device__ __attribute__((always_inline)) void serial_steps(const DevProg& p, in
         } while (stage);
         __syncthreads();
       }
-      // flat steps: a lane takes the q outputs that differ in the highest
-      // digit (their offsets are decoded once), or, where a level has no more
-      // outputs than the workgroup has lanes, a single one
+      // flat steps: a lane takes the outputs of an item, or, where a level has
+      // no more outputs than the workgroup has lanes, a single one
       const int32_t of0 = j0 ? rl(f_end, j0 - 1) : 0, of1 = rl(f_end, j1 - 1);
       const bool single = of1 - of0 <= kBlock;
       const int32_t l_end = single ? f_end : i_end;
@@ -951,15 +1010,17 @@ __device__ __attribute__((always_inline)) void serial_steps(const DevProg& p, in
       for (int32_t x0 = (single ? of0 : j0 ? rl(i_end, j0 - 1) : 0) + 64 * wv; x0 < x1; x0 += kBlock) {
         const int32_t x = min(x0 + lane, x1 - 1);
         const FlatRec r = s_rec[lane_of(l_end, x, j0, j1)];
-        const int32_t o = x - (single ? r.o_start : r.i_start);
-        const int32_t n_t = single || r.R == 0 ? 1 : q;
+        const int32_t i = x - (single ? r.o_start : r.i_start);
         const bool write = x0 + lane < x1;
-        if (!__any(r.ha >= 0 || r.hb >= 0))
-          flat_item<0, T>(r, s_dig, o, n_t, (uint32_t)q, m18, arena, lds, st, write);
-        else if (!__any(r.ha < 0 || r.hb < 0))
-          flat_item<1, T>(r, s_dig, o, n_t, (uint32_t)q, m18, arena, lds, st, write);
-        else
-          flat_item<2, T>(r, s_dig, o, n_t, (uint32_t)q, m18, arena, lds, st, write);
+        auto item = [&](auto f_) {
+          constexpr int F = decltype(f_)::value;
+          if (single) flat_item<F, 1, T>(r, s_dig, i, q, m18, arena, lds, st, write);
+          else if (nt == 2) flat_item<F, 2, T>(r, s_dig, i, q, m18, arena, lds, st, write);
+          else flat_item<F, 3, T>(r, s_dig, i, q, m18, arena, lds, st, write);
+        };
+        if (!__any(r.ha >= 0 || r.hb >= 0)) item(std::integral_constant<int, 0>{});
+        else if (!__any(r.ha < 0 || r.hb < 0)) item(std::integral_constant<int, 1>{});
+        else item(std::integral_constant<int, 2>{});
       }
       const int32_t u0 = j0 ? rl(u_end, j0 - 1) : 0, u1 = rl(u_end, j1 - 1);
       if (u0 < u1) {
@@ -1683,37 +1744,49 @@ __device__ __attribute__((always_inline)) void reduce_step(const DevProg& p, con
 template <class T>
 __device__ __attribute__((always_inline)) void knot_final(const DevProg& p, const KnotDesc& kd, Cx<T>* arena, Cx<T>* lds,
                            kn_scalar* zout, const States& st, int32_t slice) {
-  if (threadIdx.x != 0) return;
+  // the first wavefront: lane l multiplies values l, l + 64, ... of the
+  // components, the factors and q for each isolated spin, then the lanes'
+  // products are multiplied pairwise (one thread for all of them: 9 us of a
+  // 600-crossing knot's 218)
+  const int32_t lane = task_tid();
+  if (lane >= 64) return;
   const ImgHeader& h = *p.h;
   const Cx<double>* xe = p.weights + kd.w_off;
   const Cx<double>* xm = xe + kd.n_edges;
   Cx<double> z{1.0, 0.0};
   int64_t e = 0;
-  for (int i = 0; i < kd.n_comps; ++i) {
-    const int32_t t = p.comps[kd.comp_off + i];
-    const Cx<T> r = *tptr<T>(p.tens[t], arena, lds);
-    int32_t sh;
-    int64_t et;
-    if (st.local(t)) st.get(t, sh, et);
-    else st.get_late(t, sh, et);
-    e += et;
-    acc_mul(z, e, Cx<double>{(double)r.re, (double)r.im});
-  }
-  for (int i = 0; i < kd.n_factors; ++i) {
-    const Factor f = p.factors[kd.factor_off + i];
-    Cx<double> x = f.kind == FAC_LOOP ? xe[f.id]
-                   : f.kind == FAC_CONST ? plan_consts(p, kd)[f.id]
-                                         : xm[f.id];
-    if (f.kind == FAC_LEAF) x.re += (double)(kd.q - 1);
-    if (f.kind == FAC_PAIR) {  // equal fixed values: x_m, else 1
-      int sa = slice, sb = slice;
-      for (int r = 0; r < f.a; ++r) sa /= kd.q;
-      for (int r = 0; r < f.b; ++r) sb /= kd.q;
-      if (sa % kd.q != sb % kd.q) x = Cx<double>{1.0, 0.0};
+  const int32_t n_val = kd.n_comps + kd.n_factors + kd.n_iso;
+  for (int32_t i = lane; i < n_val; i += 64) {
+    Cx<double> x{(double)kd.q, 0.0};
+    if (i < kd.n_comps) {
+      const int32_t t = p.comps[kd.comp_off + i];
+      const Cx<T> r = *tptr<T>(p.tens[t], arena, lds);
+      int32_t sh;
+      int64_t et;
+      if (st.local(t)) st.get(t, sh, et);
+      else st.get_late(t, sh, et);
+      e += et;
+      x = Cx<double>{(double)r.re, (double)r.im};
+    } else if (i - kd.n_comps < kd.n_factors) {
+      const Factor f = p.factors[kd.factor_off + i - kd.n_comps];
+      x = f.kind == FAC_LOOP ? xe[f.id] : f.kind == FAC_CONST ? plan_consts(p, kd)[f.id] : xm[f.id];
+      if (f.kind == FAC_LEAF) x.re += (double)(kd.q - 1);
+      if (f.kind == FAC_PAIR) {  // equal fixed values: x_m, else 1
+        int sa = slice, sb = slice;
+        for (int r = 0; r < f.a; ++r) sa /= kd.q;
+        for (int r = 0; r < f.b; ++r) sb /= kd.q;
+        if (sa % kd.q != sb % kd.q) x = Cx<double>{1.0, 0.0};
+      }
     }
     acc_mul(z, e, x);
   }
-  for (int i = 0; i < kd.n_iso; ++i) acc_mul(z, e, Cx<double>{(double)kd.q, 0.0});
+  for (int32_t m = 32; m >= 1; m >>= 1) {
+    if (m >= n_val) continue;  // (those lanes' products are 1)
+    const Cx<double> y{__shfl_xor(z.re, m, 64), __shfl_xor(z.im, m, 64)};
+    e += __shfl_xor(e, m, 64);
+    acc_mul(z, e, y);
+  }
+  if (lane != 0) return;
   kn_scalar out;
   if (__hip_atomic_load(&p.ctrl[CTRL_ERROR], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
     out.re = out.im = __builtin_nan("");
