@@ -1183,7 +1183,10 @@ __device__ inline SplitTab split_tab(int2* mem, int32_t& used, int32_t tid, int3
 // flight: offsets come from split tables in LDS, and
 //   - up to 64 contracted entries: lane k holds the offsets of entry k, a
 //     thread computes two outputs together and issues the loads of three
-//     entries of both before their products;
+//     entries of both before their products; a B of fewer entries than the
+//     tile has outputs is first copied to LDS (half of the gathered loads were
+//     B's, and a gathered load occupies the memory pipeline whether or not it
+//     hits), and the thread then computes four;
 //   - more of them: L lanes share an output, four entries each per round;
 //   - one output over a long segment (the scalar product that ends a knot's
 //     contraction, split over many tasks): all wavefronts, an equal part of
@@ -1194,7 +1197,7 @@ __device__ inline SplitTab split_tab(int2* mem, int32_t& used, int32_t tid, int3
 // products, then the publish.
 template <class T>
 __device__ __attribute__((always_inline)) void tile_step(const DevProg& p, const StepDesc& s, int32_t tile_id, int32_t q,
-                          Cx<T>* arena, uint8_t* smem, const States& st, T* s_red, int64_t* ph) {
+                          Cx<T>* arena, uint8_t* smem, int32_t smem_bytes, const States& st, T* s_red, int64_t* ph) {
   const int32_t tid = task_tid();
   const int32_t lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   constexpr int32_t kWaves = kBlock / 64;
@@ -1208,6 +1211,7 @@ __device__ __attribute__((always_inline)) void tile_step(const DevProg& p, const
   const int32_t o0 = t * s.tile;
   const int32_t o1 = (int32_t)min((int64_t)o0 + s.tile, outs);
   // LDS: partial sums of the wavefronts, strides, tables
+  constexpr int32_t kTileFixed = kWaves * (int32_t)sizeof(Cx<double>) + 64 * (int32_t)sizeof(int2);
   LdsCx<double>* part = (LdsCx<double>*)smem;
   int2* dig = reinterpret_cast<int2*>(smem + kWaves * sizeof(Cx<double>));
   const int32_t R = rb + rm + rn;
@@ -1237,6 +1241,14 @@ __device__ __attribute__((always_inline)) void tile_step(const DevProg& p, const
   int32_t used = 0;
   const SplitTab to = split_tab(mem, used, tid, o0, o1, dig, R, D);
   const SplitTab tk_ = split_tab(mem, used, tid, k0, k1, dig + R, rk, D);
+  // B, if it has no more entries than the tile has outputs and fits
+  const int32_t L = lanes_per_output(o1 - o0, nk);
+  const int64_t size_b = (int64_t)s.nb * s.nk * s.nn;
+  LdsCx<T>* stg = (LdsCx<T>*)(mem + ((used + 1) & ~1));
+  const bool b_lds = L == 1 && nk <= 64 && size_b <= o1 - o0 &&
+                     size_b * (int32_t)sizeof(Cx<T>) <= smem_bytes - (kTileFixed + 8 * (used + 1));
+  if (b_lds)
+    for (int32_t i = tid; i < (int32_t)size_b; i += kBlock) put(stg, i, ldc((const GlbCx<T>*)(arena + s.home_b) + i));
   __syncthreads();
   int64_t tk = 0;
   if (ph) {
@@ -1276,7 +1288,46 @@ __device__ __attribute__((always_inline)) void tile_step(const DevProg& p, const
     }
     return Cx<T>{c.re + c2.re, c.im + c2.im};
   };
-  const int32_t L = lanes_per_output(o1 - o0, nk);
+  // the products of a short contracted index, NO outputs per thread at once
+  auto short_k = [&](auto no_, auto qb) {
+    constexpr int NO = decltype(no_)::value;
+    const int2 dk = lane < nk ? tk_.at(k0 + lane) : int2{0, 0};
+    for (int32_t o = o0 + tid; o < o1; o += NO * kBlock) {
+      int2 f[NO];
+      Cx<T> c[NO];
+#pragma unroll
+      for (int j = 0; j < NO; ++j) {
+        f[j] = to.at(min(o + j * kBlock, o1 - 1));
+        c[j] = zero;
+      }
+      auto macs = [&](auto nk_, int32_t k) {
+        constexpr int NK = decltype(nk_)::value;
+        Cx<T> x[NO][NK], y[NO][NK];
+#pragma unroll
+        for (int j = 0; j < NO; ++j)
+#pragma unroll
+          for (int i = 0; i < NK; ++i) {
+            x[j][i] = y[j][i] = zero;
+            if (o + j * kBlock < o1) {
+              x[j][i] = ldc(pa + (f[j].x + rl(dk.x, k + i)));
+              y[j][i] = ldc(qb + (f[j].y + rl(dk.y, k + i)));
+            }
+          }
+#pragma unroll
+        for (int i = 0; i < NK; ++i)
+#pragma unroll
+          for (int j = 0; j < NO; ++j) cfma(c[j], x[j][i], y[j][i]);
+      };
+      int32_t k = 0;
+#pragma unroll 1
+      for (; k + 3 <= nk; k += 3) macs(std::integral_constant<int, 3>{}, k);
+#pragma unroll 1
+      for (; k < nk; ++k) macs(std::integral_constant<int, 1>{}, k);
+#pragma unroll
+      for (int j = 0; j < NO; ++j)
+        if (o + j * kBlock < o1) store(o + j * kBlock, c[j]);
+    }
+  };
   if (o1 - o0 == 1 && nk >= 2 * kBlock) {
     const int32_t run = (nk + kWaves - 1) / kWaves;
     const int32_t kw0 = min(k1, k0 + wv * run), kw1 = min(k1, kw0 + run);
@@ -1299,46 +1350,8 @@ __device__ __attribute__((always_inline)) void tile_step(const DevProg& p, const
       store(o0, c);
     }
   } else if (L == 1 && nk <= 64) {
-    const int2 dk = lane < nk ? tk_.at(k0 + lane) : int2{0, 0};
-    for (int32_t o = o0 + tid; o < o1; o += 2 * kBlock) {
-      const int32_t o2 = o + kBlock;
-      const bool two = o2 < o1;
-      const int2 f = to.at(o), f2 = two ? to.at(o2) : f;
-      Cx<T> c = zero, c2 = zero;
-      int32_t k = 0;
-      for (; k + 3 <= nk; k += 3) {
-        Cx<T> x[3], y[3], x2[3], y2[3];
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-          const int32_t ka = rl(dk.x, k + j), kb = rl(dk.y, k + j);
-          x[j] = ldc(pa + (f.x + ka));
-          y[j] = ldc(pb + (f.y + kb));
-          x2[j] = y2[j] = zero;
-          if (two) {
-            x2[j] = ldc(pa + (f2.x + ka));
-            y2[j] = ldc(pb + (f2.y + kb));
-          }
-        }
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-          cfma(c, x[j], y[j]);
-          cfma(c2, x2[j], y2[j]);
-        }
-      }
-      for (; k < nk; ++k) {
-        const int32_t ka = rl(dk.x, k), kb = rl(dk.y, k);
-        const Cx<T> x = ldc(pa + (f.x + ka)), y = ldc(pb + (f.y + kb));
-        Cx<T> x2 = zero, y2 = zero;
-        if (two) {
-          x2 = ldc(pa + (f2.x + ka));
-          y2 = ldc(pb + (f2.y + kb));
-        }
-        cfma(c, x, y);
-        cfma(c2, x2, y2);
-      }
-      store(o, c);
-      if (two) store(o2, c2);
-    }
+    if (b_lds) short_k(std::integral_constant<int, 4>{}, (const LdsCx<T>*)stg);
+    else short_k(std::integral_constant<int, 2>{}, pb);
   } else {
     const int32_t lsub = tid & (L - 1);
     for (int32_t o = o0 + tid / L; o < o1; o += kBlock / L) {
@@ -2228,7 +2241,7 @@ __global__ __launch_bounds__(kBlock, 2) void engine(const uint8_t* __restrict__ 
       else if (sd.mode == STEP_GEMM64)
         gemm_tile<T, true>(p, sd, td.count, q, arena, kn_dyn_smem, dyn, st, s_red, ph);
       else
-        tile_step<T>(p, sd, td.count, q, arena, kn_dyn_smem, st, s_red, ph);
+        tile_step<T>(p, sd, td.count, q, arena, kn_dyn_smem, dyn, st, s_red, ph);
       if (ph) ph[3] = 0;
     }
     // ---- publish; the last task of a group releases the knot's next group.
