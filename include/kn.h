@@ -186,9 +186,9 @@ void kn_tait_free(kn_tait* g);
  *               split into tiles over workgroups too, whatever its
  *               multiply-add count: with a short contracted index its time on
  *               one workgroup is set by rounds of gathered loads, one round
- *               per 512 outputs (0 = default 12; 31 = by multiply-adds only).
+ *               per 512 outputs (0 = default 13; 31 = by multiply-adds only).
  * tile_outs_log2  most outputs one tile of a tiled step computes, 2^value
- *               (0 = default 10).
+ *               (0 = default 11).
  * bucket        per intermediate-size bucket overrides of the tile shape: a
  *               step whose output C has at most 2^8, 2^12, 2^16, 2^20 or more
  *               entries takes bucket 0, 1, 2, 3 or 4, and any non-zero field

@@ -48,8 +48,14 @@ int64_t elem_bytes(int32_t precision) { return precision == 1 ? 8 : 16; }
 constexpr double kMaxTiles = 1024;
 constexpr double kMaxTileOutputs = 1 << 24;  // outputs of one tile (2^28 bytes in complex128)
 constexpr int32_t kTileMacsLog2 = 15;    // multiply-adds a tile of outputs aims at
-constexpr int32_t kTileOutsLog2 = 10;    // most outputs of one tile
-constexpr int32_t kBigOutsLog2 = 12;     // steps with this many outputs are tiled
+// Most outputs of one tile: 2048 are one round of four per thread (wide grid
+// walk 12.34 ms with 2^10, 12.14 with 2^11, 12.21 with 2^12).
+constexpr int32_t kTileOutsLog2 = 11;
+// Steps with this many outputs are tiled: below, the tasks' claims and releases
+// (some 8 us with the group's) cost more than one workgroup's rounds (gradients
+// of 8 knots 397 us with 2^12, 359 with 2^13 or more; wide grid walk 12.37 ms
+// with 2^12, 12.06 with 2^13, 12.16 with none).
+constexpr int32_t kBigOutsLog2 = 13;
 
 // Intermediate-size bucket of a step (its output C): at most 2^8, 2^12,
 // 2^16, 2^20 entries, or more.

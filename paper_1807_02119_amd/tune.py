@@ -63,8 +63,8 @@ BUCKET_SPACE = {
     "gemm_tasks_log2": [3, 4, 5, 6, 7, 30],
 }
 N_BUCKETS = 5
-DEFAULTS = {"big_step_macs_log2": 16, "big_step_outs_log2": 12, "tile_macs_log2": 15,
-            "tile_outs_log2": 10, "lds_bytes": 98304, "gemm_tasks_log2": 5, "gemm64_pct": 300,
+DEFAULTS = {"big_step_macs_log2": 16, "big_step_outs_log2": 13, "tile_macs_log2": 15,
+            "tile_outs_log2": 11, "lds_bytes": 98304, "gemm_tasks_log2": 5, "gemm64_pct": 300,
             "split_serial_log2": 40, "split_min_log2": 12, "fork_serial_log2": 10, "grid": 0}
 DEFAULTS_KEY = json.dumps(DEFAULTS, sort_keys=True)
 TUNED_DIR = os.path.join(os.path.dirname(os.path.abspath(__file__)), "tuned")
