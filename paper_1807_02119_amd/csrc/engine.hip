@@ -291,15 +291,20 @@ __device__ inline int32_t wave_scan(int32_t v) {
 }
 
 // The lane in [lo, hi) whose run of items holds item x, from the inclusive
-// sums `end` of the lanes' runs (bisection: the lanes of [lo, hi) that end at
-// or before x).
+// sums `end` of the lanes' runs; x does not decrease from lane to lane and is
+// below hi's last sum.  The runs that end within the wavefront's 64 items are
+// counted one by one (few of them mostly; a bisection over the lanes is six
+// dependent shuffles).
 __device__ inline int32_t lane_of(int32_t end, int32_t x, int32_t lo, int32_t hi) {
-  int32_t j = lo;
-  for (int32_t h = 1 << (31 - __clz(hi - lo)); h >= 1; h >>= 1) {
-    const int32_t e = __shfl(end, min(j + h, hi) - 1, 64);  // (every lane takes part)
-    if (j + h <= hi && e <= x) j += h;
+  const int32_t lane = threadIdx.x & 63;
+  const int32_t x_first = __builtin_amdgcn_readlane(x, 0), x_last = __builtin_amdgcn_readlane(x, 63);
+  int32_t j = lo + __popcll(__ballot(lane >= lo && lane < hi && end <= x_first));
+  int32_t at = j;
+  for (int32_t e = __builtin_amdgcn_readlane(end, j); e <= x_last; e = __builtin_amdgcn_readlane(end, j)) {
+    at += x >= e ? 1 : 0;
+    ++j;
   }
-  return j;
+  return at;
 }
 
 template <class T>
@@ -512,8 +517,7 @@ __device__ inline T step_scale(const States& st, int32_t a, int32_t b, int64_t& 
 //     where a level has more outputs than the workgroup has lanes;
 //   - only a level ends with a barrier: an output's shift is the maximum over
 //     its entries, kept by an LDS atomic.
-// Steps with a long contracted index (more than two spins, or three where the
-// outputs are many) run as units: 2^l
+// Steps with a long contracted index (for their outputs) run as units: 2^l
 // lanes share an output, and units of up to about kUnitMacs multiply-adds are
 // taken by the wavefronts in turn.
 // Figures: the launch of one 600-crossing knot (q = 3, complex128) 480 -> 200 us,
@@ -694,9 +698,12 @@ __device__ __attribute__((always_inline)) uint32_t unit_round(const UnitCtx<T>& 
   return top;
 }
 
-// x / d for 0 <= x < 2^15 and d >= 1, from r = 1.0f / d: x + 0.5 is 0.5 / d or
-// more away from a multiple of d, and the product is off by less than 2^-7 / d.
-__device__ inline int32_t small_div(int32_t x, float r) { return (int32_t)(((float)x + 0.5f) * r); }
+// x / d for 0 <= x < 2^15 and d >= 1: x + 0.5 is 0.5 or more away from a
+// multiple of d, so its quotient 0.5 / d from an integer, and the product with
+// the approximate reciprocal (1 ulp) is off by less than 2^-7 / d.
+__device__ inline int32_t small_div(int32_t x, int32_t d) {
+  return (int32_t)(((float)x + 0.5f) * __builtin_amdgcn_rcpf((float)d));
+}
 
 // Rows (columns) of the tiles of a level's items, for steps of digits < q.
 __device__ inline int32_t flat_tile(int32_t q) { return q == 2 || q == 4 ? 2 : 3; }
@@ -723,8 +730,8 @@ __device__ inline void flat_item(const FlatRec& r, const int2* s_dig, int32_t x,
     // the tile's first row and column in the highest digits, and its output
     // where these are zero
     const int32_t bn = rn > 0 ? (q + NT - 1) / NT : 1, bm = rm > 0 ? (q + NT - 1) / NT : 1;
-    const int32_t y = small_div(x, 1.0f / (float)bn), z = small_div(y, 1.0f / (float)bm);
-    const int32_t u = small_div(z, 1.0f / (float)r.sn), b = small_div(u, 1.0f / (float)r.sm);
+    const int32_t y = small_div(x, bn), z = small_div(y, bm);
+    const int32_t u = small_div(z, r.sn), b = small_div(u, r.sm);
     o = (b * r.nm + (u - b * r.sm)) * r.nn + (z - u * r.sn);
     j0 = (x - y * bn) * NT;
     i0 = (y - z * bm) * NT;
@@ -887,9 +894,11 @@ __device__ __attribute__((always_inline)) void serial_steps(const DevProg& p, in
            ((int64_t)outs << log_l) < (d.nk >> log_l >= 16 ? kBlock : 64))
       ++log_l;
     const int32_t pack = R | rk << 8 | log_l << 16 | (outs <= kSmallIndex && nkq <= kSmallIndex ? 1 << 24 : 0);
-    // flat: at most two contracted spins, or three where the outputs fill the
-    // workgroup (few outputs of a long contracted index are better shared by
-    // several lanes each), and every state in LDS
+    // flat: a contracted index that a lane runs through by itself, of at most
+    // two spins, or three where the outputs fill the workgroup (2187 outputs of
+    // 27 entries took 27 us as units, 6 flat; with a limit of 64 entries, so
+    // that 5^3 and 6^3 were units, mixed-q values took 1110 us for 940), and
+    // every state in LDS
     auto made_here = [&](int32_t t) { return (uint32_t)(t - st.lo) < (uint32_t)made; };
     auto in_lds = [&](int32_t t) { return st.local(t) || !made_here(t); };
     const bool flat = lane < ce && (rk <= 2 || (rk == 3 && outs >= kBlock)) && outs <= kSmallIndex && in_lds(d.a) && in_lds(d.b) && st.local(d.c);
