@@ -195,7 +195,7 @@ __device__ inline void put(const GlbOut<float>& o, int32_t i, Cx<float> v) {
 }
 // Serial tasks store plainly: most of what they write is read again by the
 // same workgroup, and scattered entries written through cost the task more
-// than the release then does (117-knot batch 930 -> 820 us, mixed-q values 1187
+// than the release then does (256-knot batch 930 -> 820 us, mixed-q values 1187
 // -> 1040 us).
 template <class T>
 __device__ inline void put(GlbCx<T>* p, int32_t i, Cx<T> v) {
@@ -522,7 +522,7 @@ __device__ inline T step_scale(const States& st, int32_t a, int32_t b, int64_t& 
 // taken by the wavefronts in turn.
 // Figures: the launch of one 600-crossing knot (q = 3, complex128) 480 -> 200 us,
 // of one 250-crossing knot with q = 5 170 -> 105 us; a 263-step run of the
-// 117-knot batch 440 -> 250 us (LDS arena of 96 KiB but for the last).
+// 256-knot batch 440 -> 250 us (LDS arena of 96 KiB but for the last).
 constexpr int32_t kUnitMacs = 1024;
 constexpr float kStageMacs = 4096.0f;
 constexpr int32_t kDigCap = kTabBuf / 2;  // digit strides (pairs) of a chunk
@@ -1195,7 +1195,9 @@ __device__ inline SplitTab split_tab(int2* mem, int32_t& used, int32_t tid, int3
 //     entries of both before their products; a B of fewer entries than the
 //     tile has outputs is first copied to LDS (half of the gathered loads were
 //     B's, and a gathered load occupies the memory pipeline whether or not it
-//     hits), and the thread then computes four;
+//     hits), and the thread then computes four (a step of 9 x 531441 outputs
+//     over 3 entries: products 18.7 -> 15.1 us a task; half the copy rate of the
+//     card when every compute unit runs such tasks);
 //   - more of them: L lanes share an output, four entries each per round;
 //   - one output over a long segment (the scalar product that ends a knot's
 //     contraction, split over many tasks): all wavefronts, an equal part of
@@ -1425,6 +1427,9 @@ struct Mfma<float> {
 // region gathers half as much per product as a 64 x 64 block.  Gathers are
 // what bounds wide steps: their operands are stored in the order of the steps
 // that made them, so a wavefront's 64 entries come from up to 64 lines.
+// Rates per compute unit in complex128: K = 2187 240 GFLOP/s (280 is a large
+// library product's), K = 243 210, K = 81 170, K = 27 90-115, K = 9 45; the wide
+// grid walk 22.6 -> 20.6 ms with regions and two buffers.
 template <class T>
 struct GemmCtx {
   const GlbCx<T>* A;

@@ -53,7 +53,7 @@ constexpr int32_t kTileMacsLog2 = 15;    // multiply-adds a tile of outputs aims
 constexpr int32_t kTileOutsLog2 = 11;
 // Steps with this many outputs are tiled: below, the tasks' claims and releases
 // (some 8 us with the group's) cost more than one workgroup's rounds (gradients
-// of 8 knots 397 us with 2^12, 359 with 2^13 or more; wide grid walk 12.37 ms
+// of 32 knots 397 us with 2^12, 359 with 2^13 or more; wide grid walk 12.37 ms
 // with 2^12, 12.06 with 2^13, 12.16 with none).
 constexpr int32_t kBigOutsLog2 = 13;
 
