@@ -479,12 +479,20 @@ __device__ inline int32_t lanes_per_output(int64_t outs, int32_t nk, int32_t nth
   return L;
 }
 
+// The shift of a tensor whose entries are all subnormal: that of the least
+// normal number.  Its own exponent would make 2^-(sA+sB) overflow beside a
+// tensor of shift 0; no shift at all would leave the products subnormal, with
+// the few bits a subnormal has.
+template <class T>
+constexpr int32_t kMinShift = sizeof(T) == 8 ? -1021 : -125;
+
 template <class T>
 __device__ inline int32_t frexp_shift(T m) {
   if (!(m > 0)) return kShiftNone;
-  int s;
-  frexp((double)m, &s);
-  return s;
+  int32_t s;
+  if constexpr (sizeof(T) == 8) s = __builtin_amdgcn_frexp_exp(m);
+  else s = __builtin_amdgcn_frexp_expf(m);
+  return max(s, kMinShift<T>);
 }
 
 // Scale 2^-(sA+sB) applied to the products, and the exponent of C.
@@ -586,20 +594,6 @@ __device__ inline int2 unit_offsets(const UnitCtx<T>& u, int32_t x, int32_t d0, 
   return off;
 }
 
-// The high word of |v|: its exponent field orders magnitudes by power of two.
-__device__ inline uint32_t mag_word(double v) {
-  return (uint32_t)(__builtin_bit_cast(uint64_t, v) >> 32) & 0x7fffffffu;
-}
-__device__ inline uint32_t mag_word(float v) { return __builtin_bit_cast(uint32_t, v) & 0x7fffffffu; }
-// frexp exponent of the largest magnitude with that word (kShiftNone for
-// zeros and subnormals, 0 for infinities and NaN).
-template <class T>
-__device__ inline int32_t mag_shift(uint32_t w) {
-  constexpr int32_t kBits = sizeof(T) == 8 ? 20 : 23, kMax = sizeof(T) == 8 ? 2047 : 255;
-  const int32_t e = (int32_t)(w >> kBits);
-  return e == 0 ? kShiftNone : e == kMax ? 0 : e - (kMax / 2 - 1);
-}
-
 template <class T>
 __device__ inline void cfma(Cx<T>& c, Cx<T> a, Cx<T> b) {
   c.re = fma(a.re, b.re, c.re);
@@ -631,9 +625,9 @@ __device__ inline void load_entries(Cx<T>* arena, Cx<T>* lds, int32_t home, int3
 // NO outputs per lane (base + slot, and base + slot + one round): the loads
 // of three contracted entries of all of them are issued before their products.
 // 2^log_l lanes share an output's contracted entries.  Returns the largest
-// mag_word stored by this lane.
+// magnitude stored by this lane.
 template <int NO, class T>
-__device__ __attribute__((always_inline)) uint32_t unit_round(const UnitCtx<T>& u, Cx<T>* arena, Cx<T>* lds,
+__device__ __attribute__((always_inline)) T unit_round(const UnitCtx<T>& u, Cx<T>* arena, Cx<T>* lds,
                                                                int32_t base, int32_t lane) {
   const int32_t lsub = lane & ((1 << u.log_l) - 1);
   const int32_t nslot = 64 >> u.log_l;
@@ -683,7 +677,7 @@ __device__ __attribute__((always_inline)) uint32_t unit_round(const UnitCtx<T>& 
       c[i].im += __shfl_xor(c[i].im, m, 64);
     }
   }
-  uint32_t top = 0;
+  T top = 0;
 #pragma unroll
   for (int i = 0; i < NO; ++i) {
     const int32_t oi = o + i * nslot;
@@ -692,7 +686,7 @@ __device__ __attribute__((always_inline)) uint32_t unit_round(const UnitCtx<T>& 
       c[i].im *= u.scale;
       if (u.hc >= 0) put((GlbCx<T>*)(arena + u.hc), oi, c[i]);
       else put((LdsCx<T>*)(lds + (-1 - u.hc)), oi, c[i]);
-      top = max(top, max(mag_word(c[i].re), mag_word(c[i].im)));
+      top = fmax(top, fmax(fabs(c[i].re), fabs(c[i].im)));
     }
   }
   return top;
@@ -764,7 +758,7 @@ __device__ inline void flat_item(const FlatRec& r, const int2* s_dig, int32_t x,
     fb += j0 * col;
     o += i0 * r.sm * r.nn + j0 * r.sn;
   }
-  uint32_t mag = 0;
+  T mag = 0;
   Cx<T> c[NT][NT];
 #pragma unroll
   for (int i = 0; i < NT; ++i)
@@ -830,10 +824,10 @@ __device__ inline void flat_item(const FlatRec& r, const int2* s_dig, int32_t x,
           const int32_t oj = o + i * r.sm * r.nn + j * r.sn;
           if (r.hc < 0) put((LdsCx<T>*)(lds + (-1 - r.hc)), oj, c[i][j]);
           else put((GlbCx<T>*)(arena + r.hc), oj, c[i][j]);
-          mag = max(mag, max(mag_word(c[i][j].re), mag_word(c[i][j].im)));
+          mag = fmax(mag, fmax(fabs(c[i][j].re), fabs(c[i][j].im)));
         }
       }
-    __hip_atomic_fetch_max((__attribute__((address_space(3))) int32_t*)&st.sh[r.ic], mag_shift<T>(mag),
+    __hip_atomic_fetch_max((__attribute__((address_space(3))) int32_t*)&st.sh[r.ic], frexp_shift<T>(mag),
                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     if (o == 0) st.ex[r.ic] = st.ex[r.ia] + st.ex[r.ib] + sh;
   }
@@ -1078,20 +1072,19 @@ __device__ __attribute__((always_inline)) void serial_steps(const DevProg& p, in
                              (pk >> 24) != 0, m18,
                              (T)ldexp(1.0, -rl(sh, j)), D};
           const int32_t nslot = 64 >> u.log_l;
-          uint32_t top = 0;
+          T top = 0;
           int32_t at = u.o0;
   #pragma unroll 1
-          for (; at + nslot < u.o1; at += 2 * nslot) top = max(top, unit_round<2>(u, arena, lds, at, lane));
-          if (at < u.o1) top = max(top, unit_round<1>(u, arena, lds, at, lane));
-          const int32_t mx = wave_max_last((int32_t)top);
+          for (; at + nslot < u.o1; at += 2 * nslot) top = fmax(top, unit_round<2>(u, arena, lds, at, lane));
+          if (at < u.o1) top = fmax(top, unit_round<1>(u, arena, lds, at, lane));
+          const int32_t mx = wave_max_last(frexp_shift<T>(top));
           if (lane == 63) {
             const int32_t tc = rl(d.c, j);
             if (st.local(tc))
               __hip_atomic_fetch_max((__attribute__((address_space(3))) int32_t*)&st.sh[tc - st.lo],
-                                     mag_shift<T>((uint32_t)mx), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                                     mx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             else
-              __hip_atomic_fetch_max(&st.g[tc].shift, mag_shift<T>((uint32_t)mx), __ATOMIC_RELAXED,
-                                     __HIP_MEMORY_SCOPE_AGENT);
+              __hip_atomic_fetch_max(&st.g[tc].shift, mx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           }
           j = j_next;
         }
