@@ -189,6 +189,9 @@ void kn_tait_free(kn_tait* g);
  *               per 512 outputs (0 = default 13; 31 = by multiply-adds only).
  * tile_outs_log2  most outputs one tile of a tiled step computes, 2^value
  *               (0 = default 11).
+ *               Where the defaults of these two would take a plan past
+ *               mem_budget_bytes or KN_NOALLOC_MAX_BYTES and 12 and 10 do not,
+ *               the plan is laid out with 12 and 10.
  * bucket        per intermediate-size bucket overrides of the tile shape: a
  *               step whose output C has at most 2^8, 2^12, 2^16, 2^20 or more
  *               entries takes bucket 0, 1, 2, 3 or 4, and any non-zero field

@@ -56,6 +56,9 @@ constexpr int32_t kTileOutsLog2 = 11;
 // of 32 knots 397 us with 2^12, 359 with 2^13 or more; wide grid walk 12.37 ms
 // with 2^12, 12.06 with 2^13, 12.16 with none).
 constexpr int32_t kBigOutsLog2 = 13;
+// The values used where the default ones miss a memory limit.
+constexpr int32_t kTightTileOutsLog2 = 10;
+constexpr int32_t kTightBigOutsLog2 = 12;
 
 // Intermediate-size bucket of a step (its output C): at most 2^8, 2^12,
 // 2^16, 2^20 entries, or more.
@@ -1617,6 +1620,32 @@ static kn_plan_opts default_opts() {
   return o;
 }
 
+// Plans, lays out and sizes one knot (KN_E_BUDGET: over the memory budget, or
+// past what the device program can address).
+static kn_status plan_into(const kn_tait& g, int32_t q, const kn_plan_opts& o, kn_plan& p) {
+  const kn_status rc = kn::make_plan(g, q, o, p.k, p.stats);
+  if (rc != KN_OK) return rc;
+  kn::make_section(p.k);
+  p.k.release_planning();
+  std::vector<const kn::PlanKnot*> one{&p.k};
+  const kn::Bytes hb = kn::build_image(one, true);
+  if (hb.empty()) return KN_E_BUDGET;
+  kn::ImgHeader h;
+  std::memcpy(&h, hb.data(), sizeof(h));
+  p.laid_out = true;
+  p.stats.workspace_bytes = (uint64_t)h.workspace_bytes;
+  p.stats.image_bytes = (uint64_t)h.image_bytes;
+  p.stats.n_tasks = h.n_tasks;
+  return o.mem_budget_bytes && p.stats.workspace_bytes > o.mem_budget_bytes ? KN_E_BUDGET : KN_OK;
+}
+
+// Workspaces up to this share of KN_NOALLOC_MAX_BYTES, and up to this multiple
+// of a memory budget, are tried with the tight thresholds: of 4480 knots those
+// above 16 MB were at most 5.6 % larger with the default ones, the smallest up
+// to three times as large.
+constexpr uint64_t kScratchRetryPct = 150;
+constexpr uint64_t kBudgetRetry = 4;
+
 extern "C" kn_status kn_plan_create(const kn_tait* g, int32_t q, const kn_plan_opts* opts,
                                     kn_plan** out) {
   if (!out) return KN_E_INVALID;
@@ -1646,37 +1675,34 @@ extern "C" kn_status kn_plan_create(const kn_tait* g, int32_t q, const kn_plan_o
         b.gemm_tasks_log2 < 0 || b.gemm_tasks_log2 > 30)
       return KN_E_INVALID;
   if (o.gradient && o.slice_log2_budget) return KN_E_UNSUPPORTED;
-  kn_plan* p = new (std::nothrow) kn_plan();
+  std::unique_ptr<kn_plan> p(new (std::nothrow) kn_plan());
   if (!p) return KN_E_NOMEM;
   kn_status rc;
   try {
-    rc = kn::make_plan(*g, q, o, p->k, p->stats);
-    if (rc == KN_OK) {
-      kn::make_section(p->k);
-      p->k.release_planning();
-      std::vector<const kn::PlanKnot*> one{&p->k};
-      const kn::Bytes hb = kn::build_image(one, true);
-      if (hb.empty()) {
-        rc = KN_E_BUDGET;
-      } else {
-        kn::ImgHeader h;
-        std::memcpy(&h, hb.data(), sizeof(h));
-        p->laid_out = true;
-        p->stats.workspace_bytes = (uint64_t)h.workspace_bytes;
-        p->stats.image_bytes = (uint64_t)h.image_bytes;
-        p->stats.n_tasks = h.n_tasks;
-        if (o.mem_budget_bytes && p->stats.workspace_bytes > o.mem_budget_bytes) rc = KN_E_BUDGET;
+    rc = plan_into(*g, q, o, *p);
+    // A layout with the default step thresholds that misses a memory limit is
+    // made again with those that need the least: fewer steps run inside
+    // serial tasks, whose levels keep more tensors alive at once.
+    const uint64_t w = p->stats.workspace_bytes;
+    const bool over_budget = rc == KN_E_BUDGET && p->k.arena_elems > 0 &&
+                             w / kBudgetRetry <= o.mem_budget_bytes;
+    const bool over_scratch = rc == KN_OK && !o.gradient && w > KN_NOALLOC_MAX_BYTES &&
+                              w <= KN_NOALLOC_MAX_BYTES * kScratchRetryPct / 100;
+    if ((over_budget || over_scratch) && (!o.big_step_outs_log2 || !o.tile_outs_log2)) {
+      kn_plan_opts tight = o;
+      if (!o.big_step_outs_log2) tight.big_step_outs_log2 = kn::kTightBigOutsLog2;
+      if (!o.tile_outs_log2) tight.tile_outs_log2 = kn::kTightTileOutsLog2;
+      std::unique_ptr<kn_plan> t(new kn_plan());
+      const kn_status rt = plan_into(*g, q, tight, *t);
+      if (rt == KN_OK && (over_budget || t->stats.workspace_bytes <= KN_NOALLOC_MAX_BYTES)) {
+        p.swap(t);
+        rc = rt;
       }
     }
   } catch (const std::bad_alloc&) {
-    delete p;
     return KN_E_NOMEM;
   }
-  if (rc == KN_OK || rc == KN_E_BUDGET) {
-    *out = p;
-    return rc;
-  }
-  delete p;
+  if (rc == KN_OK || rc == KN_E_BUDGET) *out = p.release();
   return rc;
 }
 
