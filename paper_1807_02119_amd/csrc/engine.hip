@@ -339,14 +339,6 @@ __device__ inline QDiv qdiv_of(int32_t q) {
   return QDiv(q, (uint32_t)(__builtin_ldexp(1.0, 31 + l) / (double)q) + 1u, l - 1);
 }
 
-// Lane u's value of a double held per lane (uniform result).
-__device__ inline double rl_double(double x, int u) {
-  const uint64_t b = __builtin_bit_cast(uint64_t, x);
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int32_t)(uint32_t)b, u);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int32_t)(uint32_t)(b >> 32), u);
-  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
-}
-
 template <class T>
 __device__ __attribute__((always_inline)) void knot_setup(const DevProg& p, const KnotDesc& kd, Cx<T>* arena, Cx<T>* lds,
                            LdsCx<double>* s_w, int32_t w_cap, const double* J, const States& st, int32_t slice) {
@@ -565,7 +557,10 @@ struct UnitCtx {
   QDiv D;
 };
 
-// Offsets in A and B of index x < q^n over n digits from d0.  Four digits at a
+// Offsets in A and B of index x < q^n over n digits from d0; called with every
+// lane of the wavefront on, like all code that reads another lane's register
+// (one copied or spilled under a partial mask would hold nothing of the lanes
+// that are off).  Four digits at a
 // time without a branch: a taken branch costs a lone wavefront as much as
 // several digits, and the digits past the last are zero.
 template <class T>
@@ -641,8 +636,12 @@ __device__ __attribute__((always_inline)) T unit_round(const UnitCtx<T>& u, Cx<T
     f[i] = unit_offsets(u, min(o + i * nslot, u.o1 - 1), 0, u.R);
     c[i] = Cx<T>{0, 0};
   }
-  for (int32_t kk = lsub; kk < u.nkq; kk += 1 << u.log_l) {
+  for (int32_t kk0 = 0; kk0 < u.nkq; kk0 += 1 << u.log_l) {
+    // (every lane decodes, for the strides are read from other lanes'
+    // registers; one past the end repeats the last entry and adds nothing)
+    const int32_t kk = min(kk0 + lsub, u.nkq - 1);
     const int2 kf = u.nkq > 1 ? unit_offsets(u, kk, u.R + 1, u.rk - 1) : int2{0, 0};
+    if (kk0 + lsub >= u.nkq) continue;
     // the entries of the lowest contracted digit at value kk of the others
     int32_t d = 0;
 #pragma unroll 1
@@ -1078,8 +1077,8 @@ __device__ __attribute__((always_inline)) void serial_steps(const DevProg& p, in
           for (; at + nslot < u.o1; at += 2 * nslot) top = fmax(top, unit_round<2>(u, arena, lds, at, lane));
           if (at < u.o1) top = fmax(top, unit_round<1>(u, arena, lds, at, lane));
           const int32_t mx = wave_max_last(frexp_shift<T>(top));
+          const int32_t tc = rl(d.c, j);
           if (lane == 63) {
-            const int32_t tc = rl(d.c, j);
             if (st.local(tc))
               __hip_atomic_fetch_max((__attribute__((address_space(3))) int32_t*)&st.sh[tc - st.lo],
                                      mx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -1296,7 +1295,9 @@ __device__ __attribute__((always_inline)) void tile_step(const DevProg& p, const
   auto short_k = [&](auto no_, auto qb) {
     constexpr int NO = decltype(no_)::value;
     const int2 dk = lane < nk ? tk_.at(k0 + lane) : int2{0, 0};
-    for (int32_t o = o0 + tid; o < o1; o += NO * kBlock) {
+    // (a wavefront leaves the loop as a whole: macs reads all lanes' dk)
+    for (int32_t ow = o0 + 64 * wv; ow < o1; ow += NO * kBlock) {
+      const int32_t o = ow + lane;
       int2 f[NO];
       Cx<T> c[NO];
 #pragma unroll
@@ -1307,14 +1308,17 @@ __device__ __attribute__((always_inline)) void tile_step(const DevProg& p, const
       auto macs = [&](auto nk_, int32_t k) {
         constexpr int NK = decltype(nk_)::value;
         Cx<T> x[NO][NK], y[NO][NK];
+        int2 e[NK];
+#pragma unroll
+        for (int i = 0; i < NK; ++i) e[i] = int2{rl(dk.x, k + i), rl(dk.y, k + i)};
 #pragma unroll
         for (int j = 0; j < NO; ++j)
 #pragma unroll
           for (int i = 0; i < NK; ++i) {
             x[j][i] = y[j][i] = zero;
             if (o + j * kBlock < o1) {
-              x[j][i] = ldc(pa + (f[j].x + rl(dk.x, k + i)));
-              y[j][i] = ldc(qb + (f[j].y + rl(dk.y, k + i)));
+              x[j][i] = ldc(pa + (f[j].x + e[i].x));
+              y[j][i] = ldc(qb + (f[j].y + e[i].y));
             }
           }
 #pragma unroll
