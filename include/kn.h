@@ -363,7 +363,7 @@ kn_status kn_contract_noalloc(const kn_plan* p, const double* J, void* stream, k
  *   3 a tensor outside the global or the LDS arena
  *   4 spin-group extents disagree with their ranks or outputs with C's size
  *   5 the largest offset a gather can form leaves its operand
- *   6 a serial step's gather tables exceed the LDS table buffer
+ *   6 a serial step with larger spin groups or operands than serial tasks index
  *   7 the guard zone after the arena (the last 4 KiB of every workspace) was
  *     overwritten; status[3] is the first word found changed
  * The call waits for `stream` and copies the error words to the host

@@ -7,7 +7,8 @@
 // it is addressed in (the global arena or the workgroup's LDS arena), the
 // spin-group extents of each of its steps agree with their ranks, the largest
 // offset its gathers can form from the stored strides stays inside each
-// operand, and every index it holds (tensor ids, steps, tiles, reduction
+// operand, its serial steps are of a size whose offsets 24-bit multiplies form
+// exactly, and every index it holds (tensor ids, steps, tiles, reduction
 // chunks, knot and vertex records) is in range.  Offsets inside a tensor are
 // then in range by construction: the engine decodes indices below the group
 // extents only (the decode itself is pinned by its own tests).
@@ -28,7 +29,7 @@ enum CheckCode : int32_t {
   CHK_EXTENT = 3,      // a tensor outside its arena (global or LDS)
   CHK_SHAPE = 4,       // group extents disagree with ranks, or outputs with C's size
   CHK_GATHER = 5,      // the largest gathered offset leaves its operand
-  CHK_TABLE = 6,       // a serial step's gather tables exceed the LDS table buffer
+  CHK_SERIAL = 6,      // a serial step with larger spin groups or operands than serial tasks index
   CHK_GUARD = 7,       // the guard zone after the arena was overwritten
 };
 
@@ -95,8 +96,12 @@ KN_HD inline int32_t step_check(const StepDesc& d, const TensorDesc* tens, int32
   const int64_t bmax = group_max(s + rb + rm + rk, rb, q) + group_max(s + 2 * rb + rm + rk, rk, q) +
                        group_max(s + 2 * rb + rm + 2 * rk, rn, q);
   if (amax >= (int64_t)A.size || bmax >= (int64_t)B.size) return CHK_GATHER;
-  if (d.mode == STEP_SERIAL && (int64_t)2 * d.nb + d.nm + 2 * d.nk + d.nn > kTabBuf)
-    return CHK_TABLE;
+  if (d.mode == STEP_SERIAL) {
+    const int64_t bk = (int64_t)d.nb * d.nk, rows = d.nm, cols = d.nn;
+    if ((int64_t)2 * d.nb + d.nm + 2 * d.nk + d.nn > kSerialGroupMax ||
+        bk * (rows > cols ? rows : cols) > kSerialOperandMax)
+      return CHK_SERIAL;
+  }
   return CHK_OK;
 }
 

@@ -1308,9 +1308,8 @@ kn_status lay_out(PlanKnot& k, const kn_plan_opts& o, kn_plan_stats& st, int32_t
     };
     const kn_bucket_opts& bo = o.bucket[bk];
     bool big = macs >= std::ldexp(1.0, k.big_log2) || outs >= std::ldexp(1.0, k.big_outs_log2);
-    // a serial step's spin groups have at most kTabBuf entries together, and
-    // its offsets are formed from strides below 2^24; larger ones are tiled
-    if (2 * nb + nm + 2 * nk + nn > kTabBuf || std::max(nb * nm * nk, nb * nk * nn) > 16777216.0)
+    if (2 * nb + nm + 2 * nk + nn > kSerialGroupMax ||
+        std::max(nb * nm * nk, nb * nk * nn) > (double)kSerialOperandMax)
       big = true;
     if (!big) continue;
     PTiling& t = k.tiling[i];

@@ -25,8 +25,13 @@ constexpr int32_t kMagic = 0x4b4e4732;  // "KNG2"
 // engine's registers allow.
 constexpr int32_t kBlock = 512;
 // Fixed LDS areas of a workgroup (the tensor arena follows them):
-constexpr int32_t kTabBuf = 3072;   // words of the digit strides of a chunk of serial steps (and the
-                                    // most entries a serial step's spin groups may have together)
+constexpr int32_t kTabBuf = 3072;   // words of the digit strides of a chunk of serial steps
+// What a step in a serial task may have at most (larger ones are tiled): entries
+// of its spin groups together (2 nb + nm + 2 nk + nn), so that its indices and
+// the rounds of its level stay small, and entries of an operand, whose strides
+// are multiplied in 24 bits.
+constexpr int32_t kSerialGroupMax = 3072;
+constexpr int64_t kSerialOperandMax = 1 << 24;
 constexpr int32_t kDescBuf = 64;    // steps per chunk
 constexpr int32_t kStateCap = 768;  // tensor states cached for the running serial task
 

@@ -518,7 +518,7 @@ def contract_noalloc(plan: Plan, J=None, stream=None, z=None):
 
 
 CHECK_CODES = {0: "ok", 1: "queue wait time limit", 2: "task record", 3: "tensor extent",
-               4: "group shape", 5: "gather bound", 6: "table buffer", 7: "guard zone"}
+               4: "group shape", 5: "gather bound", 6: "serial step size", 7: "guard zone"}
 
 
 def workspace_status(workspace, stream=None):
