@@ -44,7 +44,8 @@ HOST_FLAGS = ["-O3", "-march=x86-64-v2", "-std=c++17", "-fPIC", "-Wall", "-Wno-u
               "-I" + os.path.join(ROOT, "include")]
 HIP_FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
              "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-             # one lane does the engine's atomics: no reduction over lanes before them
+             # no reduction over lanes before an atomic: most are done by one lane, and the
+             # lanes that fold their maxima into LDS hold few values per address
              "-mllvm", "-amdgpu-atomic-optimizer-strategy=None",
              "-I" + os.path.join(ROOT, "include")]
 

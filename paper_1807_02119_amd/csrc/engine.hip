@@ -520,8 +520,8 @@ __device__ inline T step_scale(const States& st, int32_t a, int32_t b, int64_t& 
 // Steps with a long contracted index (for their outputs) run as units: 2^l
 // lanes share an output, and units of up to about kUnitMacs multiply-adds are
 // taken by the wavefronts in turn.
-// Figures: the launch of one 600-crossing knot (q = 3, complex128) 480 -> 200 us,
-// of one 250-crossing knot with q = 5 170 -> 105 us; a 263-step run of the
+// Figures: the launch of one 574-crossing knot (q = 3, complex128) 480 -> 200 us,
+// of one 157-crossing knot with q = 5 170 -> 105 us; a 263-step run of the
 // 256-knot batch 440 -> 250 us (LDS arena of 96 KiB but for the last).
 constexpr int32_t kUnitMacs = 1024;
 constexpr float kStageMacs = 4096.0f;
@@ -1441,13 +1441,13 @@ struct GemmCtx {
   QDiv D;
 };
 
-// LDS bytes gemm_block uses.
-// Contracted entries per chunk: 8 for the largest region, whose accumulators
+// Contracted entries per chunk: half for the largest region, whose accumulators
 // leave registers for half the operands in flight.
 template <int BR, int BC>
 constexpr int32_t gemm_chunk() {
-  return BR * BC >= 128 * 128 ? 8 : 16;
+  return BR * BC >= 128 * 128 ? kGemmChunk / 2 : kGemmChunk;
 }
+// LDS bytes gemm_block uses.
 template <class T, int BR, int BC>
 constexpr int32_t gemm_lds() {
   return 2 * gemm_chunk<BR, BC>() * (BR + 1 + BC + 1) * (int32_t)sizeof(Cx<T>) + (BR + BC) * 4;
@@ -1651,6 +1651,7 @@ __device__ __attribute__((always_inline)) void gemm_tile(const DevProg& p, const
   constexpr int32_t kStr = 128;  // the decoded groups' ranks are below 32
   constexpr int32_t kOwn = W ? (gemm_lds<T, 128, 128>() > gemm_lds<T, 128, 64>() ? gemm_lds<T, 128, 128>() : gemm_lds<T, 128, 64>())
                              : (gemm_lds<T, 64, 64>() > gemm_lds<T, 128, 32>() ? gemm_lds<T, 64, 64>() : gemm_lds<T, 128, 32>());
+  static_assert(kOwn + kStr * 4 + 8 * 1024 <= kLdsLimit, "a region and 1024 contracted offsets fit");
   int32_t* str = reinterpret_cast<int32_t*>(smem + kOwn);
   int32_t* ktab = str + kStr;
   const int32_t kcap = (smem_bytes - kOwn - kStr * 4) / 8;
@@ -1771,7 +1772,7 @@ __device__ __attribute__((always_inline)) void knot_final(const DevProg& p, cons
   // the first wavefront: lane l multiplies values l, l + 64, ... of the
   // components, the factors and q for each isolated spin, then the lanes'
   // products are multiplied pairwise (one thread for all of them: 9 us of a
-  // 600-crossing knot's 218)
+  // 574-crossing knot's 218)
   const int32_t lane = task_tid();
   if (lane >= 64) return;
   const ImgHeader& h = *p.h;

@@ -1,7 +1,7 @@
 // image.cpp -- lay knot plans out as a device program (see program.h).
 //
 // Each plan is first turned into a relocatable section (make_section, run
-// once per plan, on the planning thread): descriptors, gather tables, task
+// once per plan, on the planning thread): descriptors, strides, task
 // groups and LDS homes with knot-local ids.  An image for one knot or a batch
 // is then the concatenation of sections with ids and offsets shifted
 // (build_image), which is a linear copy.
@@ -67,7 +67,9 @@ struct PGroup {
 };
 
 // Estimated time of a serial step (arbitrary units: one per step plus one per
-// 512 multiply-adds).  A task of a level-split run aims at 1/32 of the split
+// 512 multiply-adds).  It only ranks runs and subtrees against each other and
+// against the split and fork thresholds, which were tuned with it; the engine
+// runs a level's steps side by side, so a run's time is not their sum.  A task of a level-split run aims at 1/32 of the split
 // threshold, and a level has at most kSplitMaxChunks tasks.
 inline double step_est(const StepDesc& x) {
   return 1.0 + double(x.nb) * x.nm * x.nn * x.nk / 512.0;
@@ -395,9 +397,11 @@ void make_section(PlanKnot& k) {
       S.lds_used = std::max<int32_t>(S.lds_used, (int32_t)(peak * es));
     }
   }
-  // a 64 x 64 GEMM step stages two 16 x 65 operand chunks in LDS from its
-  // start, followed by the offset table of up to 1024 contracted entries; the
-  // launch's LDS must hold them (gradient plans included)
+  // lds_bytes of an image with 64 x 64 blocks covers two chunks of 16 x 65
+  // entries and the offsets of up to 1024 contracted entries.  The engine does
+  // not rely on it (a block has all of kLdsLimit, whatever lds_bytes is), but
+  // the CPU model of the images requires it; it costs the staging area a few
+  // KiB where a knot's tensors take less.
   {
     const int64_t es = elem_bytes(k.precision);
     for (const StepDesc& x : S.sd)

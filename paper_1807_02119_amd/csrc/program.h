@@ -49,12 +49,13 @@ enum TaskKind : int32_t {
 
 enum StepMode : int32_t {
   STEP_SERIAL = 0,  // done inside a serial task
-  STEP_TILES = 1,   // tiles of `tile` consecutive outputs (all L lanes per output)
-  STEP_GEMM = 2,    // 32 x 32 output blocks per batch index, LDS-staged, 2x2 per thread
-  STEP_GEMM64 = 3,  // 64 x 64 output blocks, LDS-staged, 4x4 per thread
+  STEP_TILES = 1,   // tiles of `tile` consecutive outputs
+  STEP_GEMM = 2,    // 32 x 32 output blocks per batch index, staged in LDS, multiplied on the
+                    // matrix cores; `tile` consecutive blocks per task, joined into regions
+  STEP_GEMM64 = 3,  // 64 x 64 output blocks, the same way
 };
-constexpr int32_t kGemmBlock = 32;  // rows and columns of a STEP_GEMM tile
-constexpr int32_t kGemmChunk = 16;  // contracted entries staged per LDS round
+constexpr int32_t kGemmBlock = 32;  // rows and columns of a STEP_GEMM block
+constexpr int32_t kGemmChunk = 16;  // most contracted entries staged at once
 constexpr int32_t kReduceChunk = 8192;  // outputs per task of a split step's reduction
 
 enum TaskFlags : int32_t { TF_SETUP = 1, TF_FINAL = 2 };
@@ -244,7 +245,7 @@ constexpr int32_t kLdsRec = (kLdsExp + kStates * 8 + 15) / 16 * 16;
 constexpr int32_t kLdsArena = kLdsRec + kDescBuf * kFlatRecBytes;
 // Default LDS arena of a plan (kn_plan_opts.lds_bytes).  One workgroup fills a
 // compute unit whatever it is; an arena of 24 KiB left two thirds of a
-// 600-crossing knot's operands in global memory (launch 312 us; 298 with 96 KiB).
+// 574-crossing knot's operands in global memory (launch 312 us; 298 with 96 KiB).
 constexpr int32_t kLdsDefault = 96 * 1024;
 // Dynamic LDS the engine may use, and the staging area after the tensor arena
 // (lds_bytes of it): global operands of a serial step that the whole
