@@ -224,6 +224,47 @@ def tune(pds, qs, precision=0, reps=5, space=None, grids=None, buckets=True, thr
             "table": table}
 
 
+def confirm_times(measure, best, rounds=5):
+    """The defaults and a setting, timed alternately."""
+    d_ms, b_ms = [], []
+    for _ in range(rounds):
+        d_ms.append(measure(dict(DEFAULTS)))
+        b_ms.append(measure(dict(best)))
+    return d_ms, b_ms
+
+
+def settle(rec, knob, values, measures, rounds=5, log=print):
+    """Settles one knob of a searched record over several batches: a search sees
+    one batch, whose longest chain decides.  `measures` maps a batch's seed to its
+    measure, the searched one first; the value of the least mean time over the
+    batches is taken, and the record's times are those of the settled setting."""
+    flat = flat_setting(rec["best"])
+    ms = {}
+    for v in values:
+        ms[v] = {seed: statistics.median(m(dict(flat, **{knob: v})) for _ in range(3))
+                 for seed, m in measures.items()}
+        log(f"  {knob} {v}: {ms[v]}")
+    mean = {v: statistics.mean(t.values()) for v, t in ms.items()}
+    flat[knob] = min(mean, key=mean.get)
+    d_ms, b_ms = confirm_times(next(iter(measures.values())), flat, rounds)
+    best = split_setting(flat)
+    searched = rec.get("searched", {"best": rec["best"], "best_ms": rec["best_ms"],
+                                    "confirm": rec["confirm"]})
+    table = sorted([t for t in rec["table"] if {k: v for k, v in t.items() if k != "ms"} != best]
+                   + [dict(best, ms=statistics.median(b_ms))], key=lambda t: t["ms"])
+    return dict(rec, best=best, best_ms=statistics.median(b_ms),
+                default_ms=statistics.median(d_ms),
+                confirm={"default_ms": d_ms, "best_ms": b_ms,
+                         "default_median_ms": statistics.median(d_ms),
+                         "best_median_ms": statistics.median(b_ms),
+                         "default_spread_ms": max(d_ms) - min(d_ms),
+                         "best_spread_ms": max(b_ms) - min(b_ms)},
+                settled={"knob": knob, "ms": {str(v): {str(k): x for k, x in t.items()}
+                                              for v, t in ms.items()},
+                         "mean_ms": {str(v): x for v, x in mean.items()}},
+                searched=searched, table=table)
+
+
 def save(result, path, meta):
     os.makedirs(os.path.dirname(os.path.abspath(path)), exist_ok=True)
     with open(path, "w") as f:
@@ -256,6 +297,10 @@ def main():
     ap.add_argument("--out", default=None)
     ap.add_argument("--from-tuned", action="store_true",
                     help="start the search from the setting recorded for the workload")
+    ap.add_argument("--settle", default=None, metavar="KNOB=VALUE,VALUE...",
+                    help="no search: settle one knob of the recorded settings over --seeds")
+    ap.add_argument("--seeds", default="101,102,103,104",
+                    help="batches --settle times besides the searched one")
     args = ap.parse_args()
 
     import numpy as np
@@ -267,9 +312,34 @@ def main():
         print("tune.py needs a GPU", file=sys.stderr)
         sys.exit(1)
     kn.lib()
-    knots = gen.config_knots(args.workload, args.seed, count=args.count)
-    qs = [q for _, q in knots]
-    pds = [np.ascontiguousarray(d.pd, dtype=np.int32) for d, _ in knots]
+
+    def batch(seed, count):
+        knots = gen.config_knots(args.workload, seed, count=count)
+        return ([np.ascontiguousarray(d.pd, dtype=np.int32) for d, _ in knots],
+                [q for _, q in knots])
+
+    path = args.out or os.path.join(TUNED_DIR, f"{args.workload}.json")
+    if args.settle:
+        knob, values = args.settle.split("=")
+        with open(os.path.join(TUNED_DIR, f"{args.workload}.json")) as f:
+            out = json.load(f)
+        out.pop("adjusted", None)
+        seeds = [out["seed"]] + [int(x) for x in args.seeds.split(",")]
+        batches = {seed: batch(seed, out["count"]) for seed in seeds}
+        for precision, rec in out["by_precision"].items():
+            print(f"precision {precision}", flush=True)
+            measures = {seed: make_measure(*b, precision=int(precision), reps=args.reps,
+                                           strategy=out["strategy"])
+                        for seed, b in batches.items()}
+            rec = settle(rec, knob, [int(v) for v in values.split(",")], measures,
+                         log=lambda m: print(m, flush=True))
+            print(f"{knob} {rec['best'][knob]}: {rec['best_ms']:.4f} ms "
+                  f"(defaults {rec['default_ms']:.4f} ms)", flush=True)
+            out["by_precision"][precision] = rec
+        save({}, path, out)
+        print(f"wrote {path}", flush=True)
+        return
+    pds, qs = batch(args.seed, args.count)
     cus = torch.cuda.get_device_properties(0).multi_processor_count
     out = {"workload": args.workload, "seed": args.seed, "count": args.count,
            "q": sorted(set(qs)), "strategy": args.strategy,
@@ -288,7 +358,6 @@ def main():
               + (f", start {c['start_median_ms']:.4f} ms" if "start_median_ms" in c else ""),
               flush=True)
         out["by_precision"][str(precision)] = res
-    path = args.out or os.path.join(TUNED_DIR, f"{args.workload}.json")
     save({}, path, out)
     print(f"wrote {path}", flush=True)
 
