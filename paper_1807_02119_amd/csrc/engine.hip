@@ -557,12 +557,11 @@ struct UnitCtx {
   QDiv D;
 };
 
-// Offsets in A and B of index x < q^n over n digits from d0; called with every
-// lane of the wavefront on, like all code that reads another lane's register
-// (one copied or spilled under a partial mask would hold nothing of the lanes
-// that are off).  Four digits at a
-// time without a branch: a taken branch costs a lone wavefront as much as
-// several digits, and the digits past the last are zero.
+// Offsets in A and B of index x < q^n over n digits from d0.  Called with every
+// lane of the wavefront on, like all code that reads other lanes' registers (one
+// copied or spilled under a partial mask would hold nothing of the lanes that
+// are off).  Four digits at a time without a branch: a taken branch costs a lone
+// wavefront as much as several digits, and the digits past the last are zero.
 template <class T>
 __device__ inline int2 unit_offsets(const UnitCtx<T>& u, int32_t x, int32_t d0, int32_t n) {
   int2 off{0, 0};
